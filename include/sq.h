@@ -164,6 +164,11 @@ int sq_conv2d_forward_ex(const void *in, const void *w, const float *b, float *o
  *     fits the shape can run; a smaller one only rules those algorithms out.
  *     Contents on return are unspecified; the same scratch must not be used by
  *     two calls in flight at once.
+ *   fp32 layers of 3x3 and 5x5 kernels, stride 1 and pad (K-1)/2 run on the f16 matrix
+ *   instructions when the scratch is given, every operand as the sum of two f16 values with
+ *   scales that are powers of two and fp32 sums: no less exact than the fp32 instructions
+ *   (values 2^17 and more below the largest of a neighbourhood are added up in a pass of
+ *   their own); infinities and NaN give undefined results where a window touches them.
  *   A layer with stride S >= 2 can also run as a stride-1 convolution of a
  *     space-to-depth copy of its input (S*S times the input layers, kernels of
  *     ceil(K/S) x ceil(K/S)), which the library makes in the workspace; under
@@ -307,8 +312,9 @@ int sq_fire_forward_static(const void *in, const void *w_sq, const float *b_sq,
 /*
  * The fire layer on kernels re-ordered ahead of time (section "Zero-overhead Vectorization":
  * the paper re-orders the kernels once, offline, into the order its threads read them).
- * Here the re-ordered form of the expand3x3 kernels is their minimal-filtering transform
- * G g G^T, laid out in the order the matrix-core lanes load it.
+ * Here the re-ordered form of the expand3x3 kernels is what the matrix-core lanes load: for Csq a
+ * multiple of 16 up to 64 every value as two f16 values (scaled per output layer), else the
+ * minimal-filtering transform G g G^T.
  *   sq_fire_packed_bytes(Csq, Ce3): size of that form; 0 = the shape has none (Csq not a
  *     multiple of 8 or Ce3 not a multiple of 32): use sq_fire_forward.
  *   sq_fire_pack_weights(): writes it from w_e3 [Ce3][Csq][3][3] (fp32) into `packed` (device,

@@ -145,6 +145,10 @@ int run_conv(const ConvArgs &a, int algo)
             const int rs = conv_s2d(a);
             if (rs != SQ_ERR_UNSUPPORTED) return rs;
         }
+        if (a.dtype == SQ_F32 && a.ws && !a.ws_ready) {
+            const int rp = conv_split(a);
+            if (rp != SQ_ERR_UNSUPPORTED) return rp;
+        }
         const int rc = conv_mfma(a, -1);
         if (rc != SQ_ERR_UNSUPPORTED || a.pool_H) return rc;   // only the tiled kernels pool on the way in
         return conv_direct(a);
@@ -176,12 +180,13 @@ ConvArgs make_args(const void *in, const void *w, const float *b, float *out, in
 // map of pool_H x pool_W pixels that the squeeze max-pools (3x3, stride 2) down to H x W while it reads it; with
 // cp_in as well, a column-pooled map of which the squeeze pools the rows.  cp_out: the expands write a column-pooled
 // map for the layer behind a pooling layer; SQ_ERR_UNSUPPORTED before anything is launched where
-// no kernel does that for this shape.
+// no kernel does that for this shape.  split: both expands on the f16 matrix instructions where they have a kernel for
+// the shape (split_e3: the expand3x3 kernels prepared for that, or nullptr = prepared here in conv_ws).
 int fire_impl(const void *in, const void *w_sq, const float *b_sq, const void *w_e1,
               const float *b_e1, const void *w_e3, const float *b_e3, float *out, int N, int Cin,
               int H, int W, int Csq, int Ce1, int Ce3, float *sq_map, void *conv_ws, size_t conv_ws_bytes,
               bool conv_ws_ready, const char *const *stages, int pool_H = 0, int pool_W = 0, int sq_algo = SQ_ALGO_AUTO,
-              const ColPool *cp_in = nullptr, const ColPool *cp_out = nullptr)
+              const ColPool *cp_in = nullptr, const ColPool *cp_out = nullptr, bool split = false, const void *split_e3 = nullptr)
 {
     ConvArgs a1 = make_args(sq_map, w_e1, b_e1, out, N, Csq, H, W, Ce1, 1, 1, 0, 1, Ce1 + Ce3, 0, SQ_F32);
     ConvArgs a3 = make_args(sq_map, w_e3, b_e3, out, N, Csq, H, W, Ce3, 3, 1, 1, 1, Ce1 + Ce3, Ce1, SQ_F32);
@@ -204,7 +209,9 @@ int fire_impl(const void *in, const void *w_sq, const float *b_sq, const void *w
     // expand3x3 (batches of three images and more), else both in the tiles of one direct 3x3 kernel (small
     // batches, where a fused tiling exists for the shape), else two launches.
     set_stage(stages[3]);
-    rc = conv_expand_pair(a3, a1);
+    rc = SQ_ERR_UNSUPPORTED;
+    if (split && N >= 3 && !expand_form_forced()) rc = expand_split(a3, a1, split_e3);
+    if (rc == SQ_ERR_UNSUPPORTED) rc = conv_expand_pair(a3, a1);
     if (rc == SQ_ERR_UNSUPPORTED) rc = conv_expand_fused(a3, w_e1, b_e1, Ce1, 0);
     if (rc != SQ_ERR_UNSUPPORTED) {
         set_stage("");
@@ -290,7 +297,7 @@ int sq_init(void)
     void *unused = nullptr;
     const int rs = static_scratch(&unused);
     if (rs) return rs;
-    const bool ok = conv_mfma_register_kernels() & blocked_register_kernels() & fire_bf16_register_kernels();
+    const bool ok = conv_mfma_register_kernels() & blocked_register_kernels() & split_register_kernels() & fire_bf16_register_kernels();
     if (!ok) {
         const int rc = check_launch();
         return rc ? rc : SQ_ERR_HIP;
@@ -384,6 +391,7 @@ const char *sq_conv_variant_name(int index)
 size_t sq_conv2d_workspace_bytes(int Cin, int Cout, int K, int S, int P)
 {
     if (Cin <= 0 || Cout <= 0 || K <= 0 || S < 1 || P < 0) return 0;
+    if (K == 5 && S == 1 && P == 2) return align_up(split_kernel_bytes(Cout, Cin, K), 256);
     return conv_workspace_bytes(Cin, Cout, K, S, P);
 }
 
@@ -588,11 +596,15 @@ int fire_checked(const void *in, const void *w_sq, const float *b_sq, const void
     const size_t need = packed_e3 ? map_bytes : sq_fire_workspace_bytes(N, H, W, Csq, Ce3);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need) return SQ_ERR_WORKSPACE;
     if (packed_e3 && ((uintptr_t)packed_e3 & 255)) return SQ_ERR_WORKSPACE;
+    if (packed_e3 && expand_split_shape(Csq, Ce3))   // (the other forms take these layers' kernels as they lie)
+        return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace, nullptr, 0, false,
+                         kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr, nullptr, true, packed_e3);
     if (packed_e3)
         return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace,
                          const_cast<void *>(packed_e3), conv_workspace_bytes(Csq, Ce3, 3, 1, 1), true, kFireAlone);
     return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace,
-                     (char *)workspace + map_bytes, workspace_bytes - map_bytes, false, kFireAlone);
+                     (char *)workspace + map_bytes, workspace_bytes - map_bytes, false, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr,
+                     nullptr, true);
 }
 }  // namespace
 
@@ -671,7 +683,7 @@ int sq_fire_pack_weights(const void *w_e3, void *packed, size_t packed_bytes, in
     if (((uintptr_t)packed & 255) || packed_bytes < need) return SQ_ERR_WORKSPACE;
     const KernelPrepJob job{w_e3, packed, Csq, Ce3};
     set_stage("kernel transform");
-    const int rc = conv_prepare_kernels(&job, 1, SQ_F32);
+    const int rc = expand_split_shape(Csq, Ce3) ? split_kernels((const float *)w_e3, packed, Ce3, Csq, 3) : conv_prepare_kernels(&job, 1, SQ_F32);
     set_stage("");
     return rc;
 }

@@ -407,6 +407,7 @@ const char *conv_mfma_variant_name(int i) { return kVariants[i].name; }
 // i >= 0 = tiling i.  The setter is a tuning hook, not part of the public interface.
 thread_local int g_force_expand = -2;
 extern "C" void sq_tune_force_expand(int v) { g_force_expand = v; }
+bool expand_form_forced() { return g_force_expand != -2 || g_expand_pair != -1; }
 
 // 3x3 (pad 1, stride 1) convolution a3 plus the 1x1 convolution (w1, b1, Cout1 layers) of the
 // same input, results in layers [a3.c_offset, +a3.Cout) and [coff1, +Cout1) of one tensor.

@@ -105,11 +105,23 @@ struct AvgLayout {
 size_t conv_mfma_avg_bytes(const ConvArgs &a, int variant);
 int conv_mfma_avg(const ConvArgs &a, int variant, float *sums, size_t sums_bytes, AvgLayout *lay);
 int avg_softmax(const float *sums, const AvgLayout &lay, float *means, float *probs, int N, int C, int HW);
+// fp32 3x3 and 5x5 layers of stride 1 with "same" padding on the f16 matrix instructions (split_f32.hip), their kernels
+// split in a.ws (split_kernel_bytes() bytes); SQ_ERR_UNSUPPORTED where the form does not apply or the scratch is missing.
+size_t split_kernel_bytes(int Cout, int Cin, int K);
+int conv_split(const ConvArgs &a);
+int split_kernels(const float *w, void *dst, int Cout, int Cin, int K);
+bool split_register_kernels();
+// Both expands of a fire layer (3x3 and 1x1 of one map into one tensor) in the same way, in one launch.  packed_e3: the
+// expand3x3 kernels from split_kernels(), or nullptr = split into a3.ws.
+bool expand_split_shape(int Csq, int Ce3);
+int expand_split(const ConvArgs &a3, const ConvArgs &a1, const void *packed_e3);
 // The tiling conv_mfma(a, -1) runs, or -1.
 int conv_mfma_choice(const ConvArgs &a);
 // Fused expand of a fire layer: the 3x3 convolution a3 and a 1x1 convolution of the same
 // input in one launch; SQ_ERR_UNSUPPORTED if no compiled tiling fits.
 int conv_expand_fused(const ConvArgs &a3, const void *w1, const float *b1, int Cout1, int coff1);
+// whether a tuning hook of the calling thread asks for a particular form of a fire layer's expands
+bool expand_form_forced();
 // Scratch bytes with which every algorithm can run this layer shape (0 if none needs any).
 size_t conv_workspace_bytes(int Cin, int Cout, int K, int S, int P);
 // Transforms the 3x3 kernels of n <= 8 layers (fp32) into their scratch areas in one launch;

@@ -1,0 +1,95 @@
+"""fp32 layers on the f16 matrix instructions (every operand as two f16 values): shapes at the edges of their tiles,
+magnitudes far apart, and what lies outside the forms they take."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sq():
+    import paper_1611_07151_amd as sq
+    return sq
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def assert_within_rounding(got, ref, x, w, b, pad, what):
+    """Every result within the bound of an fp32 sum over the same products: a rounding of 2^-24 per step of 16 terms (two
+    accumulators), operands and dropped products 2^-22 of each term, all relative to the sum of the terms' magnitudes."""
+    terms = oracle.conv2d(np.abs(x), np.abs(w), np.abs(b), 1, pad, False).astype(np.float64)
+    steps = w.shape[2] ** 2 * ((w.shape[1] + 15) // 16)
+    bound = (steps + 8) * 2.0 ** -23 * terms
+    err = np.abs(got.astype(np.float64) - ref)
+    assert np.isfinite(got).all() and (err <= bound).all(), (what, float((err / bound).max()))
+
+
+# N, Cin, Cout, K, H, W: one pixel, rows shorter and longer than a tile, images that share a tile, input layers that are no
+# multiple of 16, output layers that fill no block of 32, contractions dealt out to two and four wavefronts, a map that
+# does not fit LDS at once, and batches on both sides of the 32- and 96-pixel tiles
+CONVS = [(5, 16, 32, 3, 1, 1), (5, 8, 32, 3, 2, 40), (3, 24, 96, 3, 9, 7), (1, 48, 192, 3, 5, 6), (2, 64, 64, 3, 27, 27), (1, 16, 64, 3, 55, 55),
+         (9, 128, 128, 3, 3, 3), (3, 256, 384, 3, 13, 13), (1, 384, 64, 3, 40, 41), (24, 32, 96, 3, 33, 31), (2, 24, 40, 5, 11, 9),
+         (1, 3, 8, 5, 4, 70), (11, 48, 256, 5, 21, 20)]
+
+
+@pytest.mark.parametrize("case", CONVS, ids=lambda c: "x".join(map(str, c)))
+def test_conv_on_split_operands(sq, case):
+    n, cin, cout, k, h, w_ = case
+    rng = np.random.default_rng(n * 100 + cin)
+    x = synth.normal01(rng, (n, cin, h, w_))
+    w, b = synth.conv_params(rng, cout, cin, k)
+    pad = (k - 1) // 2
+    ref = oracle.conv2d(x, w, b, 1, pad, True)
+    xd, wd, bd = dev(x), dev(w), dev(b)
+    sq.sq_profile_begin(8)
+    got = sq.sq_conv2d_forward_ws(xd, wd, bd, 1, pad, True)
+    names = [r["name"] for r in sq.sq_profile_end()]
+    if cout % 32 == 0 and cin % 8 == 0:
+        assert any(f"k{k}s1_split" in s for s in names), names
+    assert_within_rounding(got.cpu().numpy(), ref, x, w, b, pad, case)
+    # into a wider tensor, without bias and ReLU
+    out = torch.full((n, cout + 5, h, w_), -7.0, device="cuda")
+    sq.sq_conv2d_forward_ws(xd, wd, None, 1, pad, False, out=out, c_offset=3)
+    assert_within_rounding(out[:, 3:3 + cout].cpu().numpy(), oracle.conv2d(x, w, None, 1, pad, False), x, w, b, pad, "offset")
+    assert bool((out[:, :3] == -7).all()) and bool((out[:, 3 + cout:] == -7).all())
+
+
+@pytest.mark.parametrize("cin", [16, 64, 384])       # one part, several parts, staged in two goes
+@pytest.mark.parametrize("outlier,scale", [(1e30, 1.0), (3e5, 1.0), (1e30, 1e-6), (1.0, 1e-30), (1e38, 1e36)])
+def test_magnitudes_far_apart_do_not_disturb_each_other(sq, cin, outlier, scale):
+    """A pixel many powers of two above its neighbours: results whose windows do not touch it keep their precision."""
+    rng = np.random.default_rng(cin)
+    x = (np.maximum(synth.normal01(rng, (2, cin, 11, 13)), 0) * np.float32(scale)).astype(np.float32)
+    x[0, 3, 4, 5] = outlier
+    x[1, :, 7, :] = 0
+    w, b = synth.conv_params(rng, 64, cin, 3)
+    w *= np.float32(0.01)
+    b *= np.float32(scale)
+    got = sq.sq_conv2d_forward_ws(dev(x), dev(w), dev(b), 1, 1, True).cpu().numpy()
+    assert_within_rounding(got, oracle.conv2d(x, w, b, 1, 1, True), x, w, b, 1, (cin, outlier, scale))
+
+
+# the expands of a fire layer: layers that fill no block, blocks shared unevenly, small and large tiles
+@pytest.mark.parametrize("n,cin,csq,ce1,ce3,h,w", [(3, 16, 16, 32, 32, 7, 7), (3, 48, 64, 40, 32, 9, 5), (7, 32, 32, 8, 96, 8, 30), (64, 64, 16, 64, 64, 3, 3),
+                                                   (3, 128, 48, 160, 160, 27, 13), (24, 32, 16, 100, 64, 33, 34)])
+def test_fire_on_split_operands(sq, n, cin, csq, ce1, ce3, h, w):
+    rng = np.random.default_rng(n + cin)
+    x = synth.uniform01(rng, (n, cin, h, w))
+    p = [*synth.conv_params(rng, csq, cin, 1), *synth.conv_params(rng, ce1, csq, 1), *synth.conv_params(rng, ce3, csq, 3)]
+    p[1] = (p[1] + 0.5).astype(np.float32)          # relu(b_sq) != 0: the padding must still be zero
+    d = [dev(a) for a in [x] + p]
+    sq.sq_profile_begin(8)
+    got = sq.sq_fire_forward(*d)
+    names = [r["name"] for r in sq.sq_profile_end()]
+    assert any("split" in s and s.endswith("+k1") for s in names), names
+    assert torch.equal(sq.sq_fire_forward_packed(*d, sq.sq_fire_pack_weights(d[5])), got)
+    s = sq.sq_conv2d_forward(d[0], d[1], d[2], 1, 0, True).cpu().numpy()
+    g = got.cpu().numpy()
+    assert_within_rounding(g[:, :ce1], oracle.conv2d(s, p[2], p[3], 1, 0, True), s, p[2], p[3], 0, "expand1x1")
+    assert_within_rounding(g[:, ce1:], oracle.conv2d(s, p[4], p[5], 1, 1, True), s, p[4], p[5], 1, "expand3x3")
