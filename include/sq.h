@@ -312,8 +312,8 @@ int sq_fire_forward_static(const void *in, const void *w_sq, const float *b_sq,
 /*
  * The fire layer on kernels re-ordered ahead of time (section "Zero-overhead Vectorization":
  * the paper re-orders the kernels once, offline, into the order its threads read them).
- * Here the re-ordered form of the expand3x3 kernels is what the matrix-core lanes load: for Csq a
- * multiple of 16 up to 64 every value as two f16 values (scaled per output layer), else the
+ * Here the re-ordered form of the expand3x3 kernels is what the matrix-core lanes load: for Csq
+ * 48 or 64 every value as two f16 values (scaled per output layer), else the
  * minimal-filtering transform G g G^T.
  *   sq_fire_packed_bytes(Csq, Ce3): size of that form; 0 = the shape has none (Csq not a
  *     multiple of 8 or Ce3 not a multiple of 32): use sq_fire_forward.

@@ -145,7 +145,8 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
     const int plane = (p.CK >> 3) * p.TP;
     int *const rows = reinterpret_cast<int *>(patch + p.patch_elems);            // [8 wavefronts][32] scales' exponents of a 1x1 block
     uint32_t *const red = reinterpret_cast<uint32_t *>(rows + 8 * 32);           // [8 wavefronts][2]
-    int2 *const bias = reinterpret_cast<int2 *>(red + 16);                       // [units][cwn][32] (scale's exponent, bias)
+    uint32_t *const pixel_top = red + 16;                                        // [TP, even] largest magnitude of a pixel
+    int2 *const bias = reinterpret_cast<int2 *>(pixel_top + ((p.TP + 1) & ~1));  // [units][cwn][32] (scale's exponent, bias)
 
     const int t = threadIdx.x, lane = t & 63, nthreads = (int)blockDim.x;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6), waves = nthreads >> 6;
@@ -215,12 +216,16 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
         mn = __builtin_amdgcn_readfirstlane(mn);
     };
 
-    // ---- range of the magnitudes of the patch, per group of eight layers of a pixel (groups of zeros have none)
+    // ---- range of the magnitudes of the patch: the largest of each pixel that is not zero throughout, over the pixels.
+    // (Per pixel, not per value: small values beside larger ones of the same pixel are no loss to any sum, and a pixel
+    // whose layers are all below 2^-17 of the patch's largest, but not all zero, is rare enough in the results of a ReLU
+    // that its tile may take several times as long.)
     constexpr uint32_t kWindow = 17u << 23;
     const int items = (p.CK >> 3) * p.TP;
     constexpr int kKeep = PARTS ? 0 : 10;                      // elements a thread holds from the scan to the split
     uint32_t mx = 0, mn = 0xffffffffu;
     bool one_window;
+    auto pixel_of = [&](int e) { return e - fdiv(e, p.dTP) * p.TP; };
     auto put = [&](int e, const float (&v)[8], float s) {
         u32x4 hi, lo;
         split8(v, s, hi, lo);
@@ -240,20 +245,27 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
             const float *b = one ? p.b1 : p.bk;
             bias[e] = int2{!one && m < p.Cout ? p.sk[m] : 0, b && m < (one ? p.Cout1 : p.Cout) ? __builtin_bit_cast(int, b[m]) : 0};
         }
-        auto scan = [&](const float (&v)[8]) {
+        for (int e = t; e < p.TP; e += nthreads) pixel_top[e] = 0;
+        __syncthreads();
+        auto scan = [&](int e, const float (&v)[8]) {
             const uint32_t m = top_of(v);
-            mx = max(mx, m);
-            if (m) mn = min(mn, m);
+            if (m) atomicMax(&pixel_top[pixel_of(e)], m);
         };
 #pragma unroll
         for (int k = 0; k < kKeep; ++k)
-            if (t + k * nthreads < items) scan(kept[k]);
+            if (t + k * nthreads < items) scan(t + k * nthreads, kept[k]);
         for (int c0 = 0; c0 < p.Cin; c0 += p.CK)
             for (int e = t + kKeep * nthreads; e < items; e += nthreads) {
                 float v[8];
                 fetch(e, c0, v);
-                scan(v);
+                scan(e, v);
             }
+        __syncthreads();
+        for (int e = t; e < p.TP; e += nthreads) {
+            const uint32_t m = pixel_top[e];
+            mx = max(mx, m);
+            if (m) mn = min(mn, m);
+        }
         reduce(mx, mn);
         one_window = mx == 0 || mx - mn < kWindow;
         if (!PARTS && one_window) {
@@ -269,13 +281,13 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
             __syncthreads();
         }
     }
-    // splits, with scale s, what lies in the window [lo, lo + 2^17) (magnitude of its group of eight layers)
+    // splits, with scale s, the pixels whose largest magnitude lies in the window [lo, lo + 2^17)
     auto stage = [&](int c0, float s, uint32_t lo) {
         for (int e = t; e < items; e += nthreads) {
             float v[8];
             fetch(e, c0, v);
             if (!one_window) {
-                const uint32_t m = top_of(v);
+                const uint32_t m = pixel_top[pixel_of(e)];
                 if (m < lo || m - lo >= kWindow) {
 #pragma unroll
                     for (int k = 0; k < 8; ++k)
@@ -337,14 +349,11 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
                 uint32_t wmax = mx, next = 0xffffffffu;
                 if (mx - lo >= kWindow) {
                     wmax = 0;
-                    for (int c0 = 0; c0 < p.Cin; c0 += p.CK)
-                        for (int e = t; e < items; e += nthreads) {
-                            float v[8];
-                            fetch(e, c0, v);
-                            const uint32_t m = top_of(v);
-                            if (m >= lo && m - lo < kWindow) wmax = max(wmax, m);
-                            if (m >= lo && m - lo >= kWindow) next = min(next, m);
-                        }
+                    for (int e = t; e < p.TP; e += nthreads) {
+                        const uint32_t m = pixel_top[e];
+                        if (m >= lo && m - lo < kWindow) wmax = max(wmax, m);
+                        if (m >= lo && m - lo >= kWindow) next = min(next, m);
+                    }
                     reduce(wmax, next);
                 }
                 s = scale_exponent(wmax);
@@ -594,7 +603,7 @@ bool plan_expand(const ConvArgs &a, const ConvArgs *a1, const void *wk, ExpandPl
     p.TP = (int)TP; p.dTP = make_fastdiv(p.TP); p.tiles = (int)tiles;
     const size_t patch = std::max<size_t>((size_t)p.CK * per_layer, p.kg > 1 ? (size_t)pl.waves * 4096 * pl.PB : 0);
     p.patch_elems = (int)(patch / 16);
-    pl.lds = patch + kExpandFixed + units * p.cwn * 32 * 8;
+    pl.lds = patch + kExpandFixed + ((size_t)(p.TP + 1) & ~(size_t)1) * 4 + units * p.cwn * 32 * 8;
     return pl.lds <= (size_t)kLdsBytes;
 }
 
@@ -627,8 +636,12 @@ int conv_split(const ConvArgs &a)
 }
 
 // Whether the expands of a fire layer of this shape run on split operands; the kernels of the expand3x3 are then packed
-// by split_kernels().
-bool expand_split_shape(int Csq, int Ce3) { return Csq % 16 == 0 && Csq <= 64 && Ce3 % 32 == 0; }
+// by split_kernels().  From 48 input layers on: whole fire layers with packed kernels, us before / now, 48 -> 192 at 27x27
+// 20.7 / 17.3 at 3 images, 30.6 / 24.0 at 12, 37.0 / 37.7 at 24; 64 -> 256 at 27x27 33.0 / 20.0, 40.7 / 33.5, 61.2 / 47.8.
+// With 16 or 32 input layers the minimal-filtering pair is as fast or faster at half of the batches (16 -> 64 at 55x55
+// 14.4 / 16.0 at 6 images, 20.1 / 21.2 at 16; 32 -> 128 at 27x27 20.0 / 21.2 at 16): their contraction is too short for
+// the patch that has to be split first.
+bool expand_split_shape(int Csq, int Ce3) { return Csq % 16 == 0 && Csq >= 48 && Csq <= 64 && Ce3 % 32 == 0; }
 
 int expand_split(const ConvArgs &a3, const ConvArgs &a1, const void *packed_e3)
 {

@@ -76,8 +76,8 @@ def test_magnitudes_far_apart_do_not_disturb_each_other(sq, cin, outlier, scale)
 
 
 # the expands of a fire layer: layers that fill no block, blocks shared unevenly, small and large tiles
-@pytest.mark.parametrize("n,cin,csq,ce1,ce3,h,w", [(3, 16, 16, 32, 32, 7, 7), (3, 48, 64, 40, 32, 9, 5), (7, 32, 32, 8, 96, 8, 30), (64, 64, 16, 64, 64, 3, 3),
-                                                   (3, 128, 48, 160, 160, 27, 13), (24, 32, 16, 100, 64, 33, 34)])
+@pytest.mark.parametrize("n,cin,csq,ce1,ce3,h,w", [(3, 16, 48, 32, 32, 7, 7), (3, 48, 64, 40, 32, 9, 5), (7, 32, 48, 8, 96, 8, 30), (64, 64, 64, 64, 64, 3, 3),
+                                                   (3, 128, 48, 160, 160, 27, 13), (24, 32, 64, 100, 64, 33, 34)])
 def test_fire_on_split_operands(sq, n, cin, csq, ce1, ce3, h, w):
     rng = np.random.default_rng(n + cin)
     x = synth.uniform01(rng, (n, cin, h, w))
