@@ -25,6 +25,15 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_a4 __attribute__((aligned(4)));   // four floats at any fp32 address
 
+// An infinity or NaN has no hi and lo: sums that it may reach are made from the fp32 operands instead.
+__device__ __forceinline__ bool odd8(const float *v)
+{
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m = max(m, __builtin_bit_cast(uint32_t, v[k]) & 0x7fffffffu);
+    return m >= 0x7f800000u;
+}
+constexpr int kPlainRow = 1 << 30;    // in the place of a scale's exponent: an output layer whose kernels hold such a value
 // Magnitude bits of a finite value; infinities and NaN count as zero, so that they do not set a scale.
 __device__ __forceinline__ uint32_t magnitude(float v)
 {
@@ -49,6 +58,17 @@ __device__ __forceinline__ uint32_t magnitude8(const float *v)
 // over- nor underflows on the way where the product of two powers of two would.
 __device__ __forceinline__ int scale_exponent(uint32_t mag) { return min(140 - (int)(mag >> 23), 127); }
 __device__ __forceinline__ float pow2(int e) { return __builtin_bit_cast(float, (uint32_t)(e + 127) << 23); }   // -126 .. 127
+
+// Largest / smallest of a wavefront's 64 lanes, the same in all: shifts within rows of 16, then row 0's and the first two
+// rows' results passed on, by DPP (a lane that nothing is shifted into keeps its own value).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+#define SQ_STEP(ctrl) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, 0xf, 0xf, false))
+    SQ_STEP(0x111); SQ_STEP(0x112); SQ_STEP(0x114); SQ_STEP(0x118); SQ_STEP(0x142); SQ_STEP(0x143);
+#undef SQ_STEP
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) { return ~wave_max(~v); }
 
 // Two values as hi and lo pairs: one packed conversion, two subtractions that round to f16.
 __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo)

@@ -16,10 +16,10 @@ __global__ __launch_bounds__(256) void split_kernels_kernel(const float *w, u32x
                                                            FastDiv dKK, int row_in_lds)
 {
     extern __shared__ float row_lds[];
-    __shared__ uint32_t top;
+    __shared__ uint32_t top, odd;
     const int m = (int)blockIdx.x, n = Cin * KK;
     const float *row = w + (size_t)m * n;
-    if (threadIdx.x == 0) top = 0;
+    if (threadIdx.x == 0) top = odd = 0;
     __syncthreads();
     uint32_t mx = 0;
     if (m < Cout)
@@ -27,19 +27,19 @@ __global__ __launch_bounds__(256) void split_kernels_kernel(const float *w, u32x
             float v[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = e0 + 256 * k < n ? row[e0 + 256 * k] : 0.f;
+            if (odd8(v)) odd = 1;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 mx = max(mx, magnitude(v[k]));
                 if (e0 + 256 * k < row_in_lds) row_lds[e0 + 256 * k] = v[k];
             }
         }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, d, 64));
+    mx = wave_max(mx);
     if ((threadIdx.x & 63) == 0) atomicMax(&top, mx);
     __syncthreads();
     const int ex = scale_exponent(top);
     const float s = pow2(ex);
-    if (threadIdx.x == 0) exponents[m] = ex;
+    if (threadIdx.x == 0) exponents[m] = odd ? kPlainRow : ex;
     for (int e = threadIdx.x; e < G * 2 * KK; e += 256) {
         const int c8 = fdiv(e, dKK), tap = e - c8 * KK;
         float v[8];
@@ -62,6 +62,7 @@ struct ExpandParams {
     const u32x4 *wk;          // K x K kernels from split_kernels_kernel, their scales' exponents, bias or nullptr
     const int *sk;
     const float *bk;
+    const float *raw;         // the K x K kernels as given
     const float *w1, *b1;     // 1x1 kernels [Cout1][Cin] fp32 of the same input (fire layers), or nullptr
     int N, Cin, H, W, HW, PT, K, P, G, relu;
     int Cout, coff, Cout1, coff1, ldc;
@@ -144,8 +145,8 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
     u32x4 *const patch = reinterpret_cast<u32x4 *>(smem);
     const int plane = (p.CK >> 3) * p.TP;
     int *const rows = reinterpret_cast<int *>(patch + p.patch_elems);            // [8 wavefronts][32] scales' exponents of a 1x1 block
-    uint32_t *const red = reinterpret_cast<uint32_t *>(rows + 8 * 32);           // [8 wavefronts][2]
-    uint32_t *const pixel_top = red + 16;                                        // [TP, even] largest magnitude of a pixel
+    uint32_t *const red = reinterpret_cast<uint32_t *>(rows + 8 * 32);           // [8 wavefronts][2], whether the patch holds an infinity or NaN, -
+    uint32_t *const pixel_top = red + 18;                                        // [TP, even] largest magnitude of a pixel
     int2 *const bias = reinterpret_cast<int2 *>(pixel_top + ((p.TP + 1) & ~1));  // [units][cwn][32] (scale's exponent, bias)
 
     const int t = threadIdx.x, lane = t & 63, nthreads = (int)blockDim.x;
@@ -203,11 +204,8 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
     auto top_of = [&](const float (&v)[8]) { return magnitude8(v); };
     // largest and smallest over the workgroup
     auto reduce = [&](uint32_t &mx, uint32_t &mn) {
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            mx = max(mx, (uint32_t)__shfl_xor((int)mx, d, 64));
-            mn = min(mn, (uint32_t)__shfl_xor((int)mn, d, 64));
-        }
+        mx = wave_max(mx);
+        mn = wave_min(mn);
         __syncthreads();
         if (lane == 0) { red[2 * wv] = mx; red[2 * wv + 1] = mn; }
         __syncthreads();
@@ -246,9 +244,11 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
             bias[e] = int2{!one && m < p.Cout ? p.sk[m] : 0, b && m < (one ? p.Cout1 : p.Cout) ? __builtin_bit_cast(int, b[m]) : 0};
         }
         for (int e = t; e < p.TP; e += nthreads) pixel_top[e] = 0;
+        if (t == 0) red[16] = 0;
         __syncthreads();
         auto scan = [&](int e, const float (&v)[8]) {
             const uint32_t m = top_of(v);
+            if (odd8(v)) red[16] = 1;
             if (m) atomicMax(&pixel_top[pixel_of(e)], m);
         };
 #pragma unroll
@@ -312,8 +312,43 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
     const rsrc_t rout = make_rsrc(p.out, (uint32_t)((size_t)p.N * p.ldc * p.HW * 4));
     const float lowest = p.relu ? 0.f : -__builtin_inff();
 
+    // ---- a block in fp32 from memory, for layers and patches with an infinity or NaN
+    const bool odd_patch = __builtin_amdgcn_readfirstlane(red[16]) != 0;
+    auto plain = [&](const float *w, int taps, int mb, int Cout, int coff, const int2 *sb) {
+        const int reach = taps == 1 ? 0 : p.P, side = 2 * reach + 1;
+        const rsrc_t rw = make_rsrc(w, (uint32_t)(Cout * p.Cin * taps) * 4u);       // (layers past the last read zeros)
+        const uint32_t row = (uint32_t)(p.Cin * taps) * 4u, wo = (uint32_t)(mb * 32 + 4 * h) * row;
+#pragma unroll 1
+        for (int pb = 0; pb < PB; ++pb) {
+            const int gp = p0 + (grp * PB + pb) * 32 + j, gq = min(gp, p.PT - 1), n = fdiv(gq, p.dHW), pix = gq - n * p.HW, y = fdiv(pix, p.dW), x = pix - y * p.W;
+            f32x16 sum;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) sum[k] = 0.f;
+#pragma unroll 1
+            for (int c = 0; c < p.Cin; ++c)
+#pragma unroll 1
+                for (int tap = 0; tap < taps; ++tap) {
+                    const int yy = y + tap / side - reach, xx = x + tap % side - reach;
+                    const float v = yy >= 0 && yy < p.H && xx >= 0 && xx < p.W ? p.in[((size_t)n * p.Cin + c) * p.HW + yy * p.W + xx] : 0.f;
+#pragma unroll
+                    for (int k = 0; k < 16; ++k)
+                        sum[k] = __builtin_fmaf(v, buf_ld(rw, wo + (uint32_t)(c * taps + tap) * 4u, (uint32_t)(8 * (k >> 2) + (k & 3)) * row), sum[k]);
+                }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int ml = 8 * (k >> 2) + 4 * h + (k & 3), m = mb * 32 + ml;
+                if (gp < p.PT && m < Cout) p.out[((size_t)n * p.ldc + coff + m) * p.HW + pix] = fmaxf(sum[k] + __builtin_bit_cast(float, sb[ml].y), lowest);
+            }
+        }
+    };
+
     // ---- remove the scales, bias, ReLU; register 4q + i = layer 8q + 4h + i: 32 neighbouring pixels per store
-    auto finish = [&](f32x16 (&main)[PB], f32x16 (&cross)[PB], int es, int mb, int Cout, int coff, const int2 *sb, const int *scales) {
+    auto finish = [&](f32x16 (&main)[PB], f32x16 (&cross)[PB], int es, int mb, int Cout, int coff, const int2 *sb, const int *scales,
+                      const float *w, int taps) {
+        if (odd_patch || __ballot((scales ? scales[j] : sb[j].x) == kPlainRow)) {
+            plain(w, taps, mb, Cout, coff, sb);
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -422,7 +457,7 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
                             for (int i = 0; i < 4; ++i) cross[pb][4 * q + i] += v[i];
                         }
             }
-            if (mb < nbk) finish(main, cross, s, mb, p.Cout, p.coff, bias + (u * p.cwn + cw) * 32, nullptr);
+            if (mb < nbk) finish(main, cross, s, mb, p.Cout, p.coff, bias + (u * p.cwn + cw) * 32, nullptr, p.raw, K * K);
         }
         if constexpr (!PARTS) {
             // 1x1 kernels straight from memory (at most 64 input layers): lane = output layer j, eight input layers per
@@ -442,15 +477,18 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
             for (int u = 0; u < u1; ++u) {
                 const int mb = u * stride + first_block;
                 uint32_t top = 0;
+                int odd = 0;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const float v[8] = {w[g][0].x, w[g][0].y, w[g][0].z, w[g][0].w, w[g][1].x, w[g][1].y, w[g][1].z, w[g][1].w};
                     top = max(top, magnitude8(v));
+                    odd |= odd8(v);
                 }
                 top = max(top, (uint32_t)__shfl_xor((int)top, 32, 64));
+                odd |= __shfl_xor(odd, 32, 64);
                 const int ex = scale_exponent(top);
                 const float ws = pow2(ex);
-                if (h == 0) rows[wv * 32 + j] = ex;
+                if (h == 0) rows[wv * 32 + j] = odd ? kPlainRow : ex;
                 u32x4 ah[4], al[4];
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
@@ -479,7 +517,7 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
                         }
                     }
                 });
-                if (mb < nb1) finish(main, cross, s, mb, p.Cout1, p.coff1, bias + ((uk + u) * p.cwn + cw) * 32, rows + wv * 32);
+                if (mb < nb1) finish(main, cross, s, mb, p.Cout1, p.coff1, bias + ((uk + u) * p.cwn + cw) * 32, rows + wv * 32, p.w1, 1);
             }
         }
     };
@@ -527,7 +565,7 @@ long long stretch_pixels(int npx, int H, int W, int P)
     return npx + (rows - 1) * P + images * (long long)P * (W + P) + 2ll * ((long long)P * (W + P) + P);
 }
 
-constexpr size_t kExpandFixed = 8 * 32 * 4 + 16 * 4;
+constexpr size_t kExpandFixed = 8 * 32 * 4 + 18 * 4;
 
 struct ExpandPlan {
     ExpandParams p;
@@ -546,7 +584,7 @@ bool plan_expand(const ConvArgs &a, const ConvArgs *a1, const void *wk, ExpandPl
         (long long)(a.H + a.P) * (a.W + a.P) * (a.N + 1ll) >= (1ll << 30) || (long long)a.Cout * a.Cin * a.K * a.K >= kMaxBufferElems)
         return false;
     ExpandParams &p = pl.p;
-    p.in = (const float *)a.in; p.out = a.out; p.wk = (const u32x4 *)wk; p.bk = a.b;
+    p.in = (const float *)a.in; p.out = a.out; p.wk = (const u32x4 *)wk; p.raw = (const float *)a.w; p.bk = a.b;
     p.N = a.N; p.Cin = a.Cin; p.H = a.H; p.W = a.W; p.HW = a.H * a.W; p.PT = (int)PT; p.K = a.K; p.P = a.P; p.G = (a.Cin + 15) / 16;
     p.relu = a.relu; p.Cout = a.Cout; p.coff = a.c_offset; p.ldc = a.out_channels;
     p.w1 = a1 ? (const float *)a1->w : nullptr; p.b1 = a1 ? a1->b : nullptr; p.Cout1 = a1 ? a1->Cout : 0; p.coff1 = a1 ? a1->c_offset : 0;

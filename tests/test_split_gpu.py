@@ -20,11 +20,16 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-def assert_within_rounding(got, ref, x, w, b, pad, what):
+def assert_close(got, ref, what):
+    err = np.abs(got.astype(np.float64) - ref) / (1 + np.abs(ref.astype(np.float64)))
+    assert np.isfinite(got).all() and err.max() <= 1e-4, (what, float(err.max()))
+
+
+def assert_within_rounding(got, ref, x, w, b, pad, what, stride=1):
     """Every result within the bound of an fp32 sum over the same products: a rounding of 2^-24 per step of 16 terms (two
     accumulators), operands and dropped products 2^-22 of each term, all relative to the sum of the terms' magnitudes."""
-    terms = oracle.conv2d(np.abs(x), np.abs(w), np.abs(b), 1, pad, False).astype(np.float64)
-    steps = w.shape[2] ** 2 * ((w.shape[1] + 15) // 16)
+    terms = oracle.conv2d(np.abs(x), np.abs(w), np.abs(b), stride, pad, False).astype(np.float64)
+    steps = max(w.shape[2] ** 2 * ((w.shape[1] + 15) // 16), 3 * ((w[0].size + 15) // 16))    # (or three roundings per 16 terms)
     bound = (steps + 8) * 2.0 ** -23 * terms
     err = np.abs(got.astype(np.float64) - ref)
     assert np.isfinite(got).all() and (err <= bound).all(), (what, float((err / bound).max()))
@@ -93,3 +98,32 @@ def test_fire_on_split_operands(sq, n, cin, csq, ce1, ce3, h, w):
     g = got.cpu().numpy()
     assert_within_rounding(g[:, :ce1], oracle.conv2d(s, p[2], p[3], 1, 0, True), s, p[2], p[3], 0, "expand1x1")
     assert_within_rounding(g[:, ce1:], oracle.conv2d(s, p[4], p[5], 1, 1, True), s, p[4], p[5], 1, "expand3x3")
+
+
+@pytest.mark.parametrize("k,stride,cin,cout,kg", [(5, 1, 24, 64, 4), (5, 1, 200, 96, 1)])
+@pytest.mark.parametrize("where", ["map", "kernels"])
+def test_infinities_and_nan_go_where_fp32_sums_take_them(sq, k, stride, cin, cout, kg, where):
+    rng = np.random.default_rng(k + cin)
+    pad = 2
+    x = synth.normal01(rng, (2, cin, 41, 43))
+    w, b = synth.conv_params(rng, cout, cin, k)
+    if where == "map":
+        x[0, 1, 20, 21] = np.inf
+        x[1, 2, 30, 7] = np.nan
+        x[1, 0, 9, 36] = -np.inf
+    else:
+        w[5, 1, 2, 2] = np.inf
+        w[40, 2, 1, 0] = np.nan
+    xi, wi = np.where(np.isfinite(x), x, 0), np.where(np.isfinite(w), w, 0)
+    # layers and windows that such a value reaches, summed in fp32 by the kernels that take every shape
+    want = sq.sq_conv2d_forward_ex(dev(x), dev(w), dev(b), stride, pad, True, algo=sq.SQ_ALGO_DIRECT).cpu().numpy()
+    got = (sq.sq_conv2d_forward_ws if stride == 1 else sq.sq_conv2d_forward)(dev(x), dev(w), dev(b), stride, pad, True).cpu().numpy()
+    reached = oracle.conv2d((~np.isfinite(x)).astype(np.float32), np.ones_like(w), None, stride, pad, False) > 0 if where == "map" else \
+        np.broadcast_to((~np.isfinite(w)).any(axis=(1, 2, 3))[None, :, None, None], want.shape)
+    assert reached.any() and np.isinf(want[reached]).any()
+    np.testing.assert_array_equal(got[reached & ~np.isfinite(want)], want[reached & ~np.isfinite(want)])
+    np.testing.assert_array_equal(got[reached & (want == 0)], 0)
+    ref = oracle.conv2d(xi, wi, b, stride, pad, True)
+    got, ref = np.where(reached, 0, got), np.where(reached, 0, ref)
+    terms = oracle.conv2d(np.abs(xi), np.abs(wi), np.abs(b), stride, pad, False).astype(np.float64)
+    assert (np.abs(got.astype(np.float64) - ref) <= w[0].size * 2.0 ** -24 * terms).all()
