@@ -149,6 +149,8 @@ int run_conv(const ConvArgs &a, int algo)
             const int rp = conv_split(a);
             if (rp != SQ_ERR_UNSUPPORTED) return rp;
         }
+        const int r7 = conv7_split(a);
+        if (r7 != SQ_ERR_UNSUPPORTED) return r7;
         const int rc = conv_mfma(a, -1);
         if (rc != SQ_ERR_UNSUPPORTED || a.pool_H) return rc;   // only the tiled kernels pool on the way in
         return conv_direct(a);
@@ -181,12 +183,13 @@ ConvArgs make_args(const void *in, const void *w, const float *b, float *out, in
 // cp_in as well, a column-pooled map of which the squeeze pools the rows.  cp_out: the expands write a column-pooled
 // map for the layer behind a pooling layer; SQ_ERR_UNSUPPORTED before anything is launched where
 // no kernel does that for this shape.  split: both expands on the f16 matrix instructions where they have a kernel for
-// the shape (split_e3: the expand3x3 kernels prepared for that, or nullptr = prepared here in conv_ws).
+// the shape (split_e3: the expand3x3 kernels prepared for that, or nullptr = prepared here in conv_ws).  have_sq: sq_map
+// holds the squeeze map already.
 int fire_impl(const void *in, const void *w_sq, const float *b_sq, const void *w_e1,
               const float *b_e1, const void *w_e3, const float *b_e3, float *out, int N, int Cin,
               int H, int W, int Csq, int Ce1, int Ce3, float *sq_map, void *conv_ws, size_t conv_ws_bytes,
               bool conv_ws_ready, const char *const *stages, int pool_H = 0, int pool_W = 0, int sq_algo = SQ_ALGO_AUTO,
-              const ColPool *cp_in = nullptr, const ColPool *cp_out = nullptr, bool split = false, const void *split_e3 = nullptr)
+              const ColPool *cp_in = nullptr, const ColPool *cp_out = nullptr, bool split = false, const void *split_e3 = nullptr, bool have_sq = false)
 {
     ConvArgs a1 = make_args(sq_map, w_e1, b_e1, out, N, Csq, H, W, Ce1, 1, 1, 0, 1, Ce1 + Ce3, 0, SQ_F32);
     ConvArgs a3 = make_args(sq_map, w_e3, b_e3, out, N, Csq, H, W, Ce3, 3, 1, 1, 1, Ce1 + Ce3, Ce1, SQ_F32);
@@ -203,7 +206,7 @@ int fire_impl(const void *in, const void *w_sq, const float *b_sq, const void *w
         asq.cp_in = true;
         asq.cp = *cp_in;
     }
-    int rc = run_conv(asq, sq_algo);
+    int rc = have_sq ? (int)SQ_OK : run_conv(asq, sq_algo);
     if (rc) return rc;
     // Both expands in one launch: the expand1x1 tiles behind the persistent workgroups of a minimal-filtering
     // expand3x3 (batches of three images and more), else both in the tiles of one direct 3x3 kernel (small
@@ -297,7 +300,7 @@ int sq_init(void)
     void *unused = nullptr;
     const int rs = static_scratch(&unused);
     if (rs) return rs;
-    const bool ok = conv_mfma_register_kernels() & blocked_register_kernels() & split_register_kernels() & fire_bf16_register_kernels();
+    const bool ok = conv_mfma_register_kernels() & blocked_register_kernels() & split_register_kernels() & stem_register_kernels() & fire_bf16_register_kernels();
     if (!ok) {
         const int rc = check_launch();
         return rc ? rc : SQ_ERR_HIP;
@@ -798,9 +801,18 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         cp.row_stride = colpool_row_stride(Wo, shift);
         return cp;
     };
+    // conv1, pool1 and the squeeze of fire2 in one launch where nobody asks for the maps between them.  The packed call from
+    // ten images on: below that, and in the unpacked call, the layers are the ones the two calls have in common bit for bit.
+    set_stage("conv1+pool1+fire2/sq");
+    bool have_sq = false;
+    if (packed && !taps && N >= 10 && g_fuse_pools_f32 < 0) {
+        rc = stem_split((const float *)in, P(0), P(1), P(2), P(3), bufS, N, 224, 224, 2, kFires[0].sq);
+        if (rc != SQ_OK && rc != SQ_ERR_UNSUPPORTED) return rc;
+        have_sq = rc == SQ_OK;
+    }
     set_stage("conv1");
     ConvArgs a_conv1 = make_args(in, params[0], P(1), bufA, N, 3, 224, 224, 96, 7, 2, 2, 1, 96, 0, SQ_F32);
-    if (split_pools & 1) {
+    if (!have_sq && (split_pools & 1)) {
         // conv1 tiles: 2 rows x 16 columns = 8 pooled columns, 56 x 7 per image
         ConvArgs c = a_conv1;
         c.cp_out = true;
@@ -811,8 +823,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
             cp_is_pending = true;
         }
     }
-    rc = run_conv(a_conv1, SQ_ALGO_AUTO);
-    if (rc) return rc;
+    if (!have_sq && (rc = conv_mfma(a_conv1, -1))) return rc;
     if ((rc = copy_tap(taps, 0, bufA, n * 96 * 111 * 111))) return rc;
     // tiling of the squeeze behind pool `bit` when the pooled map is kept although the policy would not keep it
     auto squeeze_algo = [&](int bit, int f, int C, int H_in) {
@@ -826,7 +837,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     float *cur = bufA, *nxt = bufB;
     int pooled_from = 0;   // extent of the map `cur` before the pooling that the next squeeze is to do, or 0
     int sq_algo = squeeze_algo(1, 0, 96, 111);
-    if (fuse_pools & 1) {
+    if (have_sq || (fuse_pools & 1)) {
         pooled_from = 111;
     } else {
         set_stage("pool1");
@@ -864,7 +875,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         if (rc == SQ_ERR_UNSUPPORTED)
             rc = fire_impl(cur, params[p], P(p + 1), params[p + 2], P(p + 3), params[p + 4], P(p + 5), dst,
                            N, C, H, H, fc.sq, fc.e, fc.e, bufS, conv_ws[f], conv_ws_bytes[f], conv_ws_ready[f], kFireStages[f],
-                           pooled_from, pooled_from, sq_algo, has_cp_in ? &cp_in : nullptr, nullptr);
+                           pooled_from, pooled_from, sq_algo, has_cp_in ? &cp_in : nullptr, nullptr, false, nullptr, f == 0 && have_sq);
         sq_algo = SQ_ALGO_AUTO;
         if (rc) return rc;
         p += 6;
@@ -1182,8 +1193,16 @@ int sq_squeezenet_forward_bf16(const void *in, sq_dtype in_dtype, const void *co
     };
 
     int rc = SQ_OK;
+    // conv1, pool1 and the squeeze of fire2 in one launch where nobody asks for the maps between them (same bits)
+    bool have_sq = false;
+    if (!taps && g_fuse_pools < 0) {
+        set_stage("conv1+pool1+fire2/sq");
+        rc = stem_bf16(in, in_dtype, WP(0), B(0), WP(1), B(1), bufS, N, 224, 224, 2, kFires[0].sq);
+        if (rc != SQ_OK && rc != SQ_ERR_UNSUPPORTED) return rc;
+        have_sq = rc == SQ_OK;
+    }
     set_stage("conv1");
-    if ((rc = blocked_conv7s2(in, in_dtype, WP(0), B(0), bufA, N, 224, 224, 96, 2, 1, 96, 0))) return rc;
+    if (!have_sq && (rc = blocked_conv7s2(in, in_dtype, WP(0), B(0), bufA, N, 224, 224, 96, 2, 1, 96, 0))) return rc;
     if ((rc = tap_out(0, bufA, 96, 111))) return rc;
     // Each pooled map is read by exactly one squeeze layer, so pooling runs inside that layer's launch and the
     // pooled map is never written -- unless the caller wants to see it (taps), then the two run separately
@@ -1198,8 +1217,14 @@ int sq_squeezenet_forward_bf16(const void *in, sq_dtype in_dtype, const void *co
         const int c0 = 1 + 3 * f;
         const int which_pool = f == 0 ? 0 : f == 3 ? 1 : 2;
         // small batches: the whole fire layer in one launch (then its pooling, if any, runs on its own)
-        const bool one_launch = (g_fire_one_launch == 1 || (g_fire_one_launch == -1 && N <= kFireOneLaunchMaxBatch)) &&
+        const bool squeezed = f == 0 && have_sq;
+        const bool one_launch = !squeezed && (g_fire_one_launch == 1 || (g_fire_one_launch == -1 && N <= kFireOneLaunchMaxBatch)) &&
                                 blocked_fire_fused_supported(C, fc.sq, fc.e, fc.e, pool_pending ? (H - 3) / 2 + 1 : H);
+        if (squeezed) {
+            H = (H - 3) / 2 + 1;
+            pool_pending = false;
+            { char *t = cur; cur = nxt; nxt = t; }
+        }
         if (pool_pending && (one_launch || !((fuse_pools >> which_pool) & 1))) {
             set_stage(f == 0 ? "pool1" : f == 3 ? "pool4" : "pool8");
             if ((rc = blocked_maxpool(cur, nxt, N, C, H, H, 3, 2))) return rc;
@@ -1222,7 +1247,7 @@ int sq_squeezenet_forward_bf16(const void *in, sq_dtype in_dtype, const void *co
                 // only the squeeze reads this layer's input: the expands write over it, so that every later
                 // layer finds its maps in the same buffer as without the fusion
                 { char *t = cur; cur = nxt; nxt = t; }
-            } else {
+            } else if (!squeezed) {
                 set_stage(kFireStages[f][0]);
                 if ((rc = blocked_conv(cur, WP(c0), B(c0), bufS, N, C, H, H, fc.sq, 1, 0, 1, fc.sq, 0))) return rc;
             }

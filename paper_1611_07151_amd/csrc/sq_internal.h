@@ -115,6 +115,13 @@ bool split_register_kernels();
 // expand3x3 kernels from split_kernels(), or nullptr = split into a3.ws.
 bool expand_split_shape(int Csq, int Ce3);
 int expand_split(const ConvArgs &a3, const ConvArgs &a1, const void *packed_e3);
+// The conv1 type (7x7, stride 2, three input layers, at most 96 output layers) on 16-bit matrix instructions (stem.hip):
+// alone in fp32 (split operands), or with the max pooling and the squeeze behind it in one launch -- fp32 (out: fp32 NCHW
+// map of the squeeze) or bfloat16 (packed kernels; out: blocked map).
+int conv7_split(const ConvArgs &a);
+int stem_split(const float *in, const float *w, const float *b, const float *wsq, const float *bsq, float *out, int N, int H, int W, int P, int Csq);
+int stem_bf16(const void *in, int dtype, const void *w7, const float *b, const void *wsq, const float *bsq, void *out, int N, int H, int W, int P, int Csq);
+bool stem_register_kernels();
 // The tiling conv_mfma(a, -1) runs, or -1.
 int conv_mfma_choice(const ConvArgs &a);
 // Fused expand of a fire layer: the 3x3 convolution a3 and a 1x1 convolution of the same

@@ -100,7 +100,45 @@ def test_fire_on_split_operands(sq, n, cin, csq, ce1, ce3, h, w):
     assert_within_rounding(g[:, ce1:], oracle.conv2d(s, p[4], p[5], 1, 1, True), s, p[4], p[5], 1, "expand3x3")
 
 
-@pytest.mark.parametrize("k,stride,cin,cout,kg", [(5, 1, 24, 64, 4), (5, 1, 200, 96, 1)])
+# N, H, W, pad, Cout: smaller than a tile, one pixel, tiles cut off on either side, even and odd extents, fewer output
+# layers than a block and than all three, and more tiles than workgroups
+STEMS = [(1, 7, 7, 0, 96), (2, 5, 6, 1, 8), (1, 40, 37, 2, 96), (3, 33, 70, 3, 40), (2, 224, 224, 2, 96), (17, 96, 130, 0, 33)]
+
+
+@pytest.mark.parametrize("case", STEMS, ids=lambda c: "x".join(map(str, c)))
+def test_first_layer_on_split_operands(sq, case):
+    n, h, w_, pad, cout = case
+    rng = np.random.default_rng(n + h)
+    x = synth.uniform01(rng, (n, 3, h, w_))
+    w, b = synth.conv_params(rng, cout, 3, 7)
+    sq.sq_profile_begin(8)
+    got = sq.sq_conv2d_forward(dev(x), dev(w), dev(b), 2, pad, True)
+    names = [r["name"] for r in sq.sq_profile_end()]
+    assert any("k7s2c3_split" in s for s in names), names
+    assert_within_rounding(got.cpu().numpy(), oracle.conv2d(x, w, b, 2, pad, True), x, w, b, pad, case, 2)
+    ho, wo = got.shape[2:]
+    out = torch.full((n, cout + 5, ho, wo), -7.0, device="cuda")
+    sq.sq_conv2d_forward_ex(dev(x), dev(w), None, 2, pad, False, out=out, c_offset=3)
+    assert_within_rounding(out[:, 3:3 + cout].cpu().numpy(), oracle.conv2d(x, w, None, 2, pad, False), x, w, b, pad, "offset", 2)
+    assert bool((out[:, :3] == -7).all()) and bool((out[:, 3 + cout:] == -7).all())
+
+
+@pytest.mark.parametrize("outlier,scale", [(1e30, 1.0), (3e5, 1.0), (1.0, 1e-30), (1e38, 1e36)])
+def test_first_layer_with_magnitudes_far_apart(sq, outlier, scale):
+    rng = np.random.default_rng(3)
+    x = (synth.uniform01(rng, (2, 3, 50, 61)) * np.float32(scale)).astype(np.float32)
+    x[0, 1, 20, 33] = outlier
+    w, b = synth.conv_params(rng, 96, 3, 7)
+    w *= np.float32(0.01)
+    b *= np.float32(scale)
+    got = sq.sq_conv2d_forward(dev(x), dev(w), dev(b), 2, 2, True).cpu().numpy()
+    # (a tile with such a pixel is summed one product after another: up to a rounding per product)
+    terms = oracle.conv2d(np.abs(x), np.abs(w), np.abs(b), 2, 2, False).astype(np.float64)
+    ref = oracle.conv2d(x, w, b, 2, 2, True)
+    assert np.isfinite(got).all() and (np.abs(got.astype(np.float64) - ref) <= 160 * 2.0 ** -24 * terms).all()
+
+
+@pytest.mark.parametrize("k,stride,cin,cout,kg", [(7, 2, 3, 96, 1), (5, 1, 24, 64, 4), (5, 1, 200, 96, 1)])
 @pytest.mark.parametrize("where", ["map", "kernels"])
 def test_infinities_and_nan_go_where_fp32_sums_take_them(sq, k, stride, cin, cout, kg, where):
     rng = np.random.default_rng(k + cin)
@@ -127,3 +165,20 @@ def test_infinities_and_nan_go_where_fp32_sums_take_them(sq, k, stride, cin, cou
     got, ref = np.where(reached, 0, got), np.where(reached, 0, ref)
     terms = oracle.conv2d(np.abs(xi), np.abs(wi), np.abs(b), stride, pad, False).astype(np.float64)
     assert (np.abs(got.astype(np.float64) - ref) <= w[0].size * 2.0 ** -24 * terms).all()
+
+
+@pytest.mark.parametrize("n", [10, 13])
+def test_packed_network_whose_stem_is_one_launch(sq, n):
+    """From ten images on the packed call computes the first layer, its pooling and the first squeeze in one launch."""
+    cfg = synth.config_squeezenet(seed=50 + n, n=n)
+    params = [dev(p) for p in cfg["params"]]
+    packed = sq.sq_pack_weights(params, sq.SQ_F32)
+    x = cfg["x"].copy()
+    x[n - 1, :, 100:140, 30:60] *= np.float32(1e7)         # tiles whose magnitudes span more than one scale holds
+    sq.sq_profile_begin(64)
+    got = sq.sq_squeezenet_forward_packed(dev(x), params, packed)
+    names = {r["name"] for r in sq.sq_profile_end()}
+    assert any("k7s2c3_split+pool3s2+k1" in s for s in names), names
+    ref = oracle.squeezenet(np.concatenate([x[:1], x[n - 1:]]), cfg["params"])
+    assert_close(got[[0, n - 1]].cpu().numpy(), ref, "one-launch stem vs oracle")
+    assert_close(got.cpu().numpy(), sq.sq_squeezenet_forward(dev(x), params).cpu().numpy(), "one-launch stem vs single layers")
