@@ -607,7 +607,7 @@ int fire_checked(const void *in, const void *w_sq, const float *b_sq, const void
                          const_cast<void *>(packed_e3), conv_workspace_bytes(Csq, Ce3, 3, 1, 1), true, kFireAlone);
     return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace,
                      (char *)workspace + map_bytes, workspace_bytes - map_bytes, false, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr,
-                     nullptr, true);
+                     nullptr, expand_split_shape(Csq, Ce3));
 }
 }  // namespace
 
@@ -810,6 +810,27 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         if (rc != SQ_OK && rc != SQ_ERR_UNSUPPORTED) return rc;
         have_sq = rc == SQ_OK;
     }
+    // In the same calls, expands on split operands, their expand3x3 kernels split by one launch into the part of the workspace
+    // where the unpacked call has its transformed ones.  With 48 and 64 squeeze layers at every such batch: us before / now at
+    // 10 images 26.6 / 20.1 (fire6), 33.9 / 24.1 (fire8), 20.0 / 17.8 (fire9); at 64 images 56.5 / 46.2, 90.1 / 60.7,
+    // 33.3 / 26.3.  With 16 and 32 from 32 images on: fire3 12.7 / 16.6 at 10 images, 20.4 / 19.7 at 24, 25.8 / 20.3 at
+    // 32, 39.8 / 35.1 at 64; fire5 18.6 / 23.9 at 16, 22.8 / 21.0 at 32, 36.1 / 25.0 at 64; but fire4 not where it
+    // pools the columns for the squeeze behind (with that squeeze, at 64 images 124 / 126, at 128 248 / 294).
+    const void *split_e3[8] = {};
+    if (packed && !taps && N >= 10 && g_fuse_pools_f32 < 0 && !expand_form_forced()) {
+        SplitJob jobs[8];
+        int njobs = 0;
+        char *next = (char *)means + align_up(n * 1000 * 4, 256);
+        for (int f = 0; f < 8; ++f) {
+            const FireCfg &fc = kFires[f];
+            if (!expand_split_shape(fc.sq, fc.e) && (N < 32 || (f == 2 && (split_pools & 2)))) continue;
+            split_e3[f] = next;
+            jobs[njobs++] = SplitJob{params[2 + 6 * f + 4], next, fc.e, fc.sq, 3};
+            next += align_up(split_kernel_bytes(fc.e, fc.sq, 3), 256);
+        }
+        set_stage("kernel transform");
+        if ((rc = split_kernels(jobs, njobs))) return rc;
+    }
     set_stage("conv1");
     ConvArgs a_conv1 = make_args(in, params[0], P(1), bufA, N, 3, 224, 224, 96, 7, 2, 2, 1, 96, 0, SQ_F32);
     if (!have_sq && (split_pools & 1)) {
@@ -860,7 +881,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         const bool has_cp_in = cp_is_pending;
         cp_is_pending = false;
         rc = SQ_ERR_UNSUPPORTED;
-        if (pool_behind && (split_pools & pool_bit)) {
+        if (pool_behind && (split_pools & pool_bit) && !split_e3[f]) {
             // tile groups of the expand pair: 16 tiles of 2 x 2 pixels in a row of (H + 1) / 2, numbered through the batch
             const int TX = (H + 1) / 2;
             const ColPool cp_out = colpool_of(4, TX, TX, H);
@@ -875,7 +896,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         if (rc == SQ_ERR_UNSUPPORTED)
             rc = fire_impl(cur, params[p], P(p + 1), params[p + 2], P(p + 3), params[p + 4], P(p + 5), dst,
                            N, C, H, H, fc.sq, fc.e, fc.e, bufS, conv_ws[f], conv_ws_bytes[f], conv_ws_ready[f], kFireStages[f],
-                           pooled_from, pooled_from, sq_algo, has_cp_in ? &cp_in : nullptr, nullptr, false, nullptr, f == 0 && have_sq);
+                           pooled_from, pooled_from, sq_algo, has_cp_in ? &cp_in : nullptr, nullptr, split_e3[f] != nullptr, split_e3[f], f == 0 && have_sq);
         sq_algo = SQ_ALGO_AUTO;
         if (rc) return rc;
         p += 6;

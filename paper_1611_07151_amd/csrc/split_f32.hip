@@ -12,12 +12,32 @@ namespace split {
 // 32*mb + l % 32, input layers 16*g + 8*(l/32) .. +7; layers that do not exist are zero), scaled per output layer;
 // then the scales' exponents, one int per output layer (padded to 32).  One workgroup per output layer; its row goes
 // through LDS where it fits (row_in_lds floats), so that memory sees whole lines read and 16 bytes per store.
-__global__ __launch_bounds__(256) void split_kernels_kernel(const float *w, u32x4 *wp, int *exponents, int Cout, int Cin, int KK, int G,
-                                                           FastDiv dKK, int row_in_lds)
+constexpr int kSplitLayers = 8;
+struct SplitLayer {
+    const float *w;
+    u32x4 *wp;
+    int *exponents;
+    int Cout, Cin, KK, G;
+    FastDiv dKK;
+};
+struct SplitList {
+    SplitLayer layer[kSplitLayers];
+    int first[kSplitLayers + 1];      // workgroup (row) at which a layer starts
+    int row_in_lds;
+};
+__global__ __launch_bounds__(256) void split_kernels_kernel(const SplitList list)
 {
     extern __shared__ float row_lds[];
     __shared__ uint32_t top, odd;
-    const int m = (int)blockIdx.x, n = Cin * KK;
+    int l = 0;
+    while ((int)blockIdx.x >= list.first[l + 1]) ++l;
+    const SplitLayer &y = list.layer[l];
+    const float *const w = y.w;
+    u32x4 *const wp = y.wp;
+    int *const exponents = y.exponents;
+    const int Cout = y.Cout, Cin = y.Cin, KK = y.KK, G = y.G, row_in_lds = list.row_in_lds;
+    const FastDiv dKK = y.dKK;
+    const int m = (int)blockIdx.x - list.first[l], n = Cin * KK;
     const float *row = w + (size_t)m * n;
     if (threadIdx.x == 0) top = odd = 0;
     __syncthreads();
@@ -536,15 +556,32 @@ size_t split_kernel_bytes(int Cout, int Cin, int K)
     return mb * K * K * (((size_t)Cin + 15) / 16) * 2048 + mb * 32 * sizeof(float);
 }
 
+int split_kernels(const SplitJob *jobs, int njobs)
+{
+    SplitList list = {};
+    double bytes = 0;
+    int rows = 0, longest = 0;
+    for (int l = 0; l < njobs; ++l) {
+        const SplitJob &j = jobs[l];
+        const int mb = (j.Cout + 31) / 32, G = (j.Cin + 15) / 16, KK = j.K * j.K;
+        list.layer[l] = SplitLayer{(const float *)j.w, (u32x4 *)j.dst, reinterpret_cast<int *>((char *)j.dst + (size_t)mb * KK * G * 2048), j.Cout, j.Cin, KK, G,
+                                   make_fastdiv(KK)};
+        list.first[l] = rows;
+        rows += mb * 32;
+        longest = std::max(longest, j.Cin * KK);
+        bytes += 8.0 * j.Cout * j.Cin * KK;
+    }
+    for (int l = njobs; l <= kSplitLayers; ++l) list.first[l] = rows;
+    list.row_in_lds = std::min(longest, 15 * 1024);
+    LaunchScope scope("split_kernels", 0.0, bytes, 0.0);
+    hipLaunchKernelGGL(split_kernels_kernel, dim3(rows), dim3(256), list.row_in_lds * sizeof(float), current_stream(), list);
+    return check_launch();
+}
+
 int split_kernels(const float *w, void *dst, int Cout, int Cin, int K)
 {
-    const int mb = (Cout + 31) / 32, G = (Cin + 15) / 16, KK = K * K;
-    int *exponents = reinterpret_cast<int *>((char *)dst + (size_t)mb * KK * G * 2048);
-    const int row = std::min(Cin * KK, 15 * 1024);
-    LaunchScope scope("split_kernels", 0.0, 8.0 * Cout * Cin * KK, 0.0);
-    hipLaunchKernelGGL(split_kernels_kernel, dim3(mb * 32), dim3(256), row * sizeof(float), current_stream(), w, (u32x4 *)dst, exponents, Cout, Cin, KK, G,
-                       make_fastdiv(KK), row);
-    return check_launch();
+    const SplitJob job = {w, dst, Cout, Cin, K};
+    return split_kernels(&job, 1);
 }
 
 namespace {
@@ -673,7 +710,7 @@ int conv_split(const ConvArgs &a)
     return rc ? rc : launch_expand(pl, a, nullptr);
 }
 
-// Whether the expands of a fire layer of this shape run on split operands; the kernels of the expand3x3 are then packed
+// Whether the expands of a fire layer of this shape run on split operands at any batch; the kernels of the expand3x3 are then packed
 // by split_kernels().  From 48 input layers on: whole fire layers with packed kernels, us before / now, 48 -> 192 at 27x27
 // 20.7 / 17.3 at 3 images, 30.6 / 24.0 at 12, 37.0 / 37.7 at 24; 64 -> 256 at 27x27 33.0 / 20.0, 40.7 / 33.5, 61.2 / 47.8.
 // With 16 or 32 input layers the minimal-filtering pair is as fast or faster at half of the batches (16 -> 64 at 55x55
@@ -684,7 +721,6 @@ bool expand_split_shape(int Csq, int Ce3) { return Csq % 16 == 0 && Csq >= 48 &&
 int expand_split(const ConvArgs &a3, const ConvArgs &a1, const void *packed_e3)
 {
     ExpandPlan pl;
-    if (!expand_split_shape(a3.Cin, a3.Cout)) return SQ_ERR_UNSUPPORTED;
     void *const wk = packed_e3 ? const_cast<void *>(packed_e3) : a3.ws;
     if (!wk || ((uintptr_t)wk & 255) || (!packed_e3 && a3.ws_bytes < split_kernel_bytes(a3.Cout, a3.Cin, 3))) return SQ_ERR_UNSUPPORTED;
     if (!plan_expand(a3, &a1, wk, pl)) return SQ_ERR_UNSUPPORTED;

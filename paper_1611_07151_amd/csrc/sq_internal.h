@@ -109,6 +109,8 @@ int avg_softmax(const float *sums, const AvgLayout &lay, float *means, float *pr
 // split in a.ws (split_kernel_bytes() bytes); SQ_ERR_UNSUPPORTED where the form does not apply or the scratch is missing.
 size_t split_kernel_bytes(int Cout, int Cin, int K);
 int conv_split(const ConvArgs &a);
+struct SplitJob { const void *w; void *dst; int Cout, Cin, K; };
+int split_kernels(const SplitJob *jobs, int njobs);     // up to eight layers in one launch
 int split_kernels(const float *w, void *dst, int Cout, int Cin, int K);
 bool split_register_kernels();
 // Both expands of a fire layer (3x3 and 1x1 of one map into one tensor) in the same way, in one launch.  packed_e3: the

@@ -167,9 +167,10 @@ def test_infinities_and_nan_go_where_fp32_sums_take_them(sq, k, stride, cin, cou
     assert (np.abs(got.astype(np.float64) - ref) <= w[0].size * 2.0 ** -24 * terms).all()
 
 
-@pytest.mark.parametrize("n", [10, 13])
-def test_packed_network_whose_stem_is_one_launch(sq, n):
-    """From ten images on the packed call computes the first layer, its pooling and the first squeeze in one launch."""
+@pytest.mark.parametrize("n,split_layers", [(10, 4), (13, 4), (32, 8)])
+def test_packed_network_on_split_operands(sq, n, split_layers):
+    """From ten images on the packed call computes the first layer, its pooling and the first squeeze in one launch, and
+    the expands of the later fire layers, from 32 on of all, on split operands."""
     cfg = synth.config_squeezenet(seed=50 + n, n=n)
     params = [dev(p) for p in cfg["params"]]
     packed = sq.sq_pack_weights(params, sq.SQ_F32)
@@ -179,6 +180,7 @@ def test_packed_network_whose_stem_is_one_launch(sq, n):
     got = sq.sq_squeezenet_forward_packed(dev(x), params, packed)
     names = {r["name"] for r in sq.sq_profile_end()}
     assert any("k7s2c3_split+pool3s2+k1" in s for s in names), names
+    assert sum("/e1+e3|k3s1_split" in s for s in names) == split_layers, names
     ref = oracle.squeezenet(np.concatenate([x[:1], x[n - 1:]]), cfg["params"])
     assert_close(got[[0, n - 1]].cpu().numpy(), ref, "one-launch stem vs oracle")
     assert_close(got.cpu().numpy(), sq.sq_squeezenet_forward(dev(x), params).cpu().numpy(), "one-launch stem vs single layers")
