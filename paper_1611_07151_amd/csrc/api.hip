@@ -552,11 +552,22 @@ int sq_classifier_forward(const float *in, const float *w, const float *b, float
     ConvArgs a = make_args(in, w, b, (float *)workspace, N, Cin, H, W, Cout, 1, 1, 0, 1, Cout, 0, SQ_F32);
     AvgLayout lay;
     set_stage("classifier/conv");
-    int rc = (g_fuse_classifier < 0 ? N >= 8 : g_fuse_classifier) ? conv_mfma_avg(a, -1, (float *)workspace, workspace_bytes, &lay)
-                                                                   : (int)SQ_ERR_UNSUPPORTED;
+    const bool fuse = g_fuse_classifier < 0 ? N >= 8 : g_fuse_classifier;
+    float *sums = (float *)workspace;
+    int rc = SQ_ERR_UNSUPPORTED;
+    // on split operands where that pays and the workspace (that of the separate layers) holds the split kernels beside the
+    // plane sums, that is from about as many pixels as input layers on
+    const size_t split_bytes = align_up(split_kernel_bytes(Cout, Cin, 1), 256), split_sums = conv_avg_split_bytes(a);
+    if (fuse && split_sums && split_bytes + split_sums <= workspace_bytes && Cout <= 2048) {
+        sums = (float *)((char *)workspace + split_bytes);
+        rc = split_kernels(w, workspace, Cout, Cin, 1);
+        if (rc == SQ_OK) rc = conv_avg_split(a, workspace, sums, workspace_bytes - split_bytes, &lay);
+    } else if (fuse) {
+        rc = conv_mfma_avg(a, -1, sums, workspace_bytes, &lay);
+    }
     if (rc == SQ_OK) {
         set_stage("classifier/avgpool+softmax");
-        rc = avg_softmax((const float *)workspace, lay, means, probs, N, Cout, H * W);
+        rc = avg_softmax(sums, lay, means, probs, N, Cout, H * W);
         if (rc != SQ_ERR_UNSUPPORTED) {
             set_stage("");
             return rc;
@@ -816,9 +827,10 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     // 33.3 / 26.3.  With 16 and 32 from 32 images on: fire3 12.7 / 16.6 at 10 images, 20.4 / 19.7 at 24, 25.8 / 20.3 at
     // 32, 39.8 / 35.1 at 64; fire5 18.6 / 23.9 at 16, 22.8 / 21.0 at 32, 36.1 / 25.0 at 64; but fire4 not where it
     // pools the columns for the squeeze behind (with that squeeze, at 64 images 124 / 126, at 128 248 / 294).
-    const void *split_e3[8] = {};
+    const void *split_e3[8] = {}, *split_c10 = nullptr;
+    ConvArgs a10 = make_args(nullptr, params[50], P(51), nullptr, N, 512, 13, 13, 1000, 1, 1, 0, 1, 1000, 0, SQ_F32);
     if (packed && !taps && N >= 10 && g_fuse_pools_f32 < 0 && !expand_form_forced()) {
-        SplitJob jobs[8];
+        SplitJob jobs[9];
         int njobs = 0;
         char *next = (char *)means + align_up(n * 1000 * 4, 256);
         for (int f = 0; f < 8; ++f) {
@@ -827,6 +839,10 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
             split_e3[f] = next;
             jobs[njobs++] = SplitJob{params[2 + 6 * f + 4], next, fc.e, fc.sq, 3};
             next += align_up(split_kernel_bytes(fc.e, fc.sq, 3), 256);
+        }
+        if (g_fuse_classifier < 0 && conv_avg_split_bytes(a10)) {
+            split_c10 = next;
+            jobs[njobs++] = SplitJob{params[50], next, 1000, 512, 1};
         }
         set_stage("kernel transform");
         if ((rc = split_kernels(jobs, njobs))) return rc;
@@ -922,8 +938,10 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     // conv10 -> global average pooling -> softmax.  The convolution writes per-image plane sums of its results instead
     // of the 1000 x 13 x 13 map (which is then never written or read), and one more launch turns them into class means
     // and probabilities.  A caller who wants to see the map gets it from an extra, plain run of the convolution; means
-    // and probabilities come from the same two launches either way, so taps do not change them.
-    const ConvArgs a10 = make_args(cur, params[50], P(51), nxt, N, 512, H, H, 1000, 1, 1, 0, 1, 1000, 0, SQ_F32);
+    // and probabilities come from the same two launches either way, so taps do not change them (the packed call from ten
+    // images on excepted: its split operands are for calls without taps, and round differently).
+    a10.in = cur;
+    a10.out = nxt;
     set_stage("conv10");
     bool have_map = false;
     if (taps && taps[12]) {
@@ -932,7 +950,8 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         have_map = true;
     }
     AvgLayout lay;
-    rc = (g_fuse_classifier < 0 ? N >= 8 : g_fuse_classifier) ? conv_mfma_avg(a10, -1, bufS, n * kBufS * 4, &lay) : (int)SQ_ERR_UNSUPPORTED;
+    rc = split_c10 ? conv_avg_split(a10, split_c10, bufS, n * kBufS * 4, &lay) : (int)SQ_ERR_UNSUPPORTED;
+    if (rc == SQ_ERR_UNSUPPORTED && (g_fuse_classifier < 0 ? N >= 8 : g_fuse_classifier)) rc = conv_mfma_avg(a10, -1, bufS, n * kBufS * 4, &lay);
     if (rc == SQ_OK) {
         set_stage("avgpool+softmax");
         if ((rc = avg_softmax(bufS, lay, means, probs, N, 1000, H * H))) return rc;

@@ -70,6 +70,15 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
 }
 __device__ __forceinline__ uint32_t wave_min(uint32_t v) { return ~wave_max(~v); }
 
+// Sum over a half wavefront's 32 lanes, in its last lane (31 and 63).
+__device__ __forceinline__ float half_wave_sum(float v)
+{
+#define SQ_STEP(ctrl, rows) v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, rows, 0xf, false))
+    SQ_STEP(0x111, 0xf); SQ_STEP(0x112, 0xf); SQ_STEP(0x114, 0xf); SQ_STEP(0x118, 0xf); SQ_STEP(0x142, 0xa);
+#undef SQ_STEP
+    return v;
+}
+
 // Two values as hi and lo pairs: one packed conversion, two subtractions that round to f16.
 __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo)
 {

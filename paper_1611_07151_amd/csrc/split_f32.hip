@@ -12,7 +12,7 @@ namespace split {
 // 32*mb + l % 32, input layers 16*g + 8*(l/32) .. +7; layers that do not exist are zero), scaled per output layer;
 // then the scales' exponents, one int per output layer (padded to 32).  One workgroup per output layer; its row goes
 // through LDS where it fits (row_in_lds floats), so that memory sees whole lines read and 16 bytes per store.
-constexpr int kSplitLayers = 8;
+constexpr int kSplitLayers = 9;
 struct SplitLayer {
     const float *w;
     u32x4 *wp;

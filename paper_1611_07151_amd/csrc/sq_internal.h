@@ -110,8 +110,12 @@ int avg_softmax(const float *sums, const AvgLayout &lay, float *means, float *pr
 size_t split_kernel_bytes(int Cout, int Cin, int K);
 int conv_split(const ConvArgs &a);
 struct SplitJob { const void *w; void *dst; int Cout, Cin, K; };
-int split_kernels(const SplitJob *jobs, int njobs);     // up to eight layers in one launch
+int split_kernels(const SplitJob *jobs, int njobs);     // up to nine layers in one launch
 int split_kernels(const float *w, void *dst, int Cout, int Cin, int K);
+// The averaging form of a 1x1 layer with ReLU (as conv_mfma_avg) on the f16 matrix instructions (avg_split.hip); kernels
+// from split_kernels().
+size_t conv_avg_split_bytes(const ConvArgs &a);
+int conv_avg_split(const ConvArgs &a, const void *kernels, float *sums, size_t sums_bytes, AvgLayout *lay);
 bool split_register_kernels();
 // Both expands of a fire layer (3x3 and 1x1 of one map into one tensor) in the same way, in one launch.  packed_e3: the
 // expand3x3 kernels from split_kernels(), or nullptr = split into a3.ws.

@@ -184,3 +184,34 @@ def test_packed_network_on_split_operands(sq, n, split_layers):
     ref = oracle.squeezenet(np.concatenate([x[:1], x[n - 1:]]), cfg["params"])
     assert_close(got[[0, n - 1]].cpu().numpy(), ref, "one-launch stem vs oracle")
     assert_close(got.cpu().numpy(), sq.sq_squeezenet_forward(dev(x), params).cpu().numpy(), "one-launch stem vs single layers")
+
+
+# several images per tile and a tile per part of an image, layers staged in parts of 64 and of 128, a last workgroup that is
+# not full, and (the fp32 forms then) too little work or too small a workspace for the split kernels
+@pytest.mark.parametrize("n,cin,h,w,cout,taken", [(100, 64, 13, 13, 170, True), (9000, 128, 2, 1, 136, True), (170, 192, 9, 12, 130, True), (16, 256, 14, 14, 1000, True),
+                                                  (80, 512, 6, 5, 1100, False), (16, 64, 13, 13, 40, False), (10, 2048, 5, 5, 2048, False)])
+def test_classifier_on_split_operands(sq, n, cin, h, w, cout, taken):
+    rng = np.random.default_rng(n + cin)
+    x = synth.uniform01(rng, (n, cin, h, w))
+    x[1, cin // 2:] *= np.float32(1e6)                     # scales that change on the way
+    x[2] *= np.float32(1e-20)
+    wt, b = synth.conv_params(rng, cout, cin, 1)
+    sq.sq_profile_begin(16)
+    probs, means = sq.sq_classifier_forward(dev(x), dev(wt), dev(b), want_means=True)
+    names = [r["name"] for r in sq.sq_profile_end()]
+    assert any("k1s1_split_96+planesums" in k for k in names) == taken, names
+    ref = oracle.conv2d(x, wt, b, 1, 0, True).astype(np.float64).mean(axis=(2, 3))
+    # three roundings per 16 products and one per pixel, relative to the terms
+    terms = oracle.conv2d(np.abs(x), np.abs(wt), np.abs(b), 1, 0, False).astype(np.float64).mean(axis=(2, 3))
+    err = np.abs(means.cpu().numpy() - ref)
+    assert (err <= (3 * cin / 16 + h * w + 16) * 2.0 ** -24 * terms).all(), float((err / terms).max())
+    assert_close(probs.cpu().numpy(), oracle.softmax(means.cpu().numpy()), "softmax")
+    # an infinity and a NaN: means of the images that hold none stay, the others are those of fp32 sums
+    x[3, 1, 0, 0], x[4, 0, h - 1, w - 1] = np.inf, np.nan
+    _, odd = sq.sq_classifier_forward(dev(x), dev(wt), dev(b), want_means=True)
+    odd = odd.cpu().numpy()
+    want = sq.sq_avgpool_global(sq.sq_conv2d_forward_ex(dev(x), dev(wt), dev(b), 1, 0, True, algo=sq.SQ_ALGO_DIRECT)).cpu().numpy()
+    assert np.isinf(want[3]).any()
+    np.testing.assert_array_equal(np.isinf(odd), np.isinf(want))
+    keep = np.isfinite(want) & (np.arange(n) != 4)[:, None]
+    assert (np.abs(odd - ref)[keep & (np.arange(n) != 3)[:, None]] <= ((cin + h * w + 16) * 2.0 ** -24 * terms)[keep & (np.arange(n) != 3)[:, None]]).all()
