@@ -168,6 +168,7 @@ struct ConvParams {
     int ldcb, coffb;     // layer blocks (of 8) per image in `out`, first block written (F32OUT: layers, first layer)
     int PT;              // N*H*W
     int tiles;           // pixel tiles of 32*PB
+    int by_xcd;          // the workgroups of an XCD take neighbouring tiles
     int ncblk;           // groups of 32*CB output layers = workgroups that share a pixel range
     int Hin, Win;        // pooled-input kernel: extents of the map before the 3x3 stride-2 max pooling (H, W = after)
     FastDiv dHW, dW, dG, dK, dNcblk;
@@ -183,8 +184,9 @@ __global__ __launch_bounds__(kThreads, 2) void conv_blocked_kernel(const ConvPar
 {
     const bool second = (int)blockIdx.x >= split;
     const ConvParams p = second ? pb : pa;   // by value: every field becomes a scalar select
-    const int wg = second ? (int)blockIdx.x - split : (int)blockIdx.x;
     const int nwg = second ? (int)gridDim.x - split : split;
+    const int part_wg = second ? (int)blockIdx.x - split : (int)blockIdx.x;
+    const int wg = p.by_xcd ? xcd_remap(part_wg, nwg) : part_wg;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     u32x4 *const wl = reinterpret_cast<u32x4 *>(smem);                 // [CB][steps][64] A operands
     const int per_mb = p.steps * 64;                                      // 16-byte elements per 32 layers
@@ -712,6 +714,13 @@ struct ConvPlan {
     double flops, bytes;
 };
 
+// Whether a pair's tiles are dealt out so that neighbouring ones run on one XCD and its rows above and below meet in
+// one L2.  Expands at 64 images, us without / with: 16 -> 64 at 55x55 17.7 / 16.7, 32 -> 128 at 55x55 32.8 / 29.8; but
+// 48 -> 192 at 27x27 18.1 / 20.7, 64 -> 256 at 27x27 25.4 / 25.7, and 1x1 layers 128 -> 16 at 55x55 12.8 / 14.4,
+// 512 -> 1000 at 13x13 21.8 / 24.6, and a 3x3 layer with fp32 results at 55x55 167 / 170: with nothing to share,
+// neighbours only crowd the same channels.
+bool walks_rows(int H, int W) { return (long long)H * W >= 2048; }
+
 // Fills the launch parameters of one convolution; CB/PB/D = 0 lets this function choose.
 int plan_conv(ConvPlan &pl, const void *in, const void *wp, const float *b, void *out, int N, int Cin, int H, int W, int Cout,
               int K, int P, int relu, int ldc_channels, int c_offset, int CB, int PB, int D, bool f32_out = false)
@@ -751,6 +760,7 @@ int plan_conv(ConvPlan &pl, const void *in, const void *wp, const float *b, void
     }
     if (p.steps % D != 0) return SQ_ERR_UNSUPPORTED;
     pl.CB = CB; pl.PB = PB; pl.D = D;
+    p.by_xcd = 0;
     p.tiles = (int)((PT + 32 * PB - 1) / (32 * PB));
     p.ncblk = (Cout + 32 * CB - 1) / (32 * CB);
     p.dNcblk = make_fastdiv(p.ncblk);
@@ -832,6 +842,7 @@ int blocked_conv_pair(const void *in, const void *wp1, const float *b1, int Cout
     if ((rc = plan_conv(pk, in, wpk, bk, out, N, Cin, H, W, Coutk, K, (K - 1) / 2, relu, ldc_channels, c_offsetk, pk.CB, pk.PB, D)))
         return rc;
     if ((rc = plan_conv(p1, in, wp1, b1, out, N, Cin, H, W, Cout1, 1, 0, relu, ldc_channels, c_offset1, pk.CB, pk.PB, D))) return rc;
+    p1.p.by_xcd = pk.p.by_xcd = K > 1 && walks_rows(H, W);
     BlockedConvFn fn = kernel_for(pk.CB, pk.PB, D);
     if (!allow_lds(fn)) {
         const int e = check_launch();

@@ -394,3 +394,23 @@ def test_network_largest_batch(sq):
     with pytest.raises(sq.SqError) as e:
         sq.sq_squeezenet_forward_bf16(torch.empty((908, 3, 224, 224), device="cuda"), params, packed)
     assert e.value.status == -3
+
+
+@pytest.mark.parametrize("n,h,w,csq,ce1,ce3", [(1, 46, 45, 16, 24, 40), (7, 33, 64, 32, 128, 96), (3, 45, 45, 16, 8, 64), (40, 48, 47, 48, 64, 64)])
+def test_expands_dealt_out_by_xcd_are_the_single_layers(sq, n, h, w, csq, ce1, ce3):
+    """Maps on both sides of the size from which neighbouring tiles share an XCD, launches of any number of workgroups: every
+    tile is computed once, with the bits of the layers run one by one."""
+    rng = np.random.default_rng(n + h)
+    x = to_blocked(synth.normal01(rng, (n, 16, h, w))).cuda()
+    (w_sq, b_sq), (w_e1, b_e1), (w_e3, b_e3) = (synth.conv_params(rng, csq, 16, 1), synth.conv_params(rng, ce1, csq, 1), synth.conv_params(rng, ce3, csq, 3))
+    p = [sq.sq_blocked_pack_kernels(dev(k)) for k in (w_sq, w_e1, w_e3)]
+    try:
+        sq.lib.sq_tune_fire_one_launch(0)
+        got = sq.sq_blocked_fire_forward(x, 16, p[0], dev(b_sq), p[1], dev(b_e1), p[2], dev(b_e3), csq, ce1, ce3)
+    finally:
+        sq.lib.sq_tune_fire_one_launch(-1)
+    s = sq.sq_blocked_conv2d_forward(x, p[0], dev(b_sq), 16, csq, 1, 0, True)
+    out = torch.full_like(got, -7.0)
+    sq.sq_blocked_conv2d_forward(s, p[1], dev(b_e1), csq, ce1, 1, 0, True, out=out, c_offset=0)
+    sq.sq_blocked_conv2d_forward(s, p[2], dev(b_e3), csq, ce3, 3, 1, True, out=out, c_offset=ce1)
+    assert torch.equal(got.view(torch.int16), out.view(torch.int16))
