@@ -42,6 +42,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 FP32_MFMA_PEAK_TFLOPS = 157.3     # MI355X dense fp32 matrix peak
+F16_MFMA_PEAK_TFLOPS = 2500.0     # MI355X dense f16 matrix peak; kernels named *_split issue three f16 products per fp32 one
 HBM_PEAK_GBS = 8000.0
 FLOP_PER_IMAGE = 2 * 832_667_936  # 2 x multiply-accumulates of the 26 convolutions
 
@@ -290,19 +291,23 @@ def main() -> int:
         elif dom_name in tj.get("bytes_per_launch", {}):
             traffic, traffic_note = tj["bytes_per_launch"][dom_name], "FETCH_SIZE + WRITE_SIZE per launch, scaled by the copy calibration (profiles/hbm_traffic.md)"
     executed = dom["mfma_flops"] / dom["launches"] / (dom_ms * 1e-3) / 1e12
-    roofline = dict(bound="mfma", achieved=round(achieved, 2), peak=FP32_MFMA_PEAK_TFLOPS,
-                    unit="TFLOP/s", frac=round(achieved / FP32_MFMA_PEAK_TFLOPS, 4), traffic=traffic,
+    issue_peak = lambda kernel: F16_MFMA_PEAK_TFLOPS if "_split" in kernel else FP32_MFMA_PEAK_TFLOPS
+    dom_peak = F16_MFMA_PEAK_TFLOPS / 3 if "_split" in dom_name else FP32_MFMA_PEAK_TFLOPS
+    roofline = dict(bound="mfma", achieved=round(achieved, 2), peak=round(dom_peak, 1),
+                    unit="TFLOP/s", frac=round(achieved / dom_peak, 4), traffic=traffic,
                     traffic_note=traffic_note,
-                    executed_tflops=round(executed, 2), executed_frac=round(executed / FP32_MFMA_PEAK_TFLOPS, 4),
+                    executed_tflops=round(executed, 2), executed_frac=round(executed / issue_peak(dom_name), 4),
                     note="achieved/frac count the layer definition's 2 x MACs (algorithmic); executed_* count the "
                          "operations the kernel's MFMA instructions really issue (padding included; the "
-                         "minimal-filtering part forms 16 products where the definition has 36) = matrix-core utilisation",
+                         "minimal-filtering part forms 16 products where the definition has 36, split operands three f16 "
+                         "ones for each) against the peak of those instructions = matrix-core utilisation; peak is a third "
+                         "of the f16 peak for split operands",
                     kernel=dom_name, launches_per_step=dom["launches"] / K,
                     avg_launch_us=round(dom_ms * 1e3, 2),
                     flop_per_launch=dom["flops"] / dom["launches"],
                     mfma_flop_per_launch=dom["mfma_flops"] / dom["launches"],
                     share_of_gpu_time=round(dom["ms"] / sum(k["ms"] for k in kernels.values()), 3))
-    all_mfma = sum(k["mfma_flops"] for k in kernels.values()) / K
+    all_mfma = sum(k["mfma_flops"] / issue_peak(name) for name, k in kernels.items()) / K
     all_ms = sum(k["ms"] for k in kernels.values()) / K
     layers = {}
     for name, e in stages.items():
@@ -522,7 +527,7 @@ def main() -> int:
         "batch1_graph_images_per_sec": None if args.skip_batch1 else round(k1 / dt1g, 1),
         "batch1_graph_matches_eager": graph_ok,
         "ms_per_step_with_events": round(dt_events / K * 1e3, 4),
-        "mfma_utilisation_whole_pass": round(all_mfma / (all_ms * 1e-3) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4),
+        "mfma_utilisation_whole_pass": round(all_mfma / (all_ms * 1e-3) / 1e12, 4),
         "roofline": roofline, "cpu_baseline": cpu, "energy": energy, "reduced_precision": reduced,
         "layer_sweep_bf16_batch256": sweep, "modules": modules, "layers": layers,
     }

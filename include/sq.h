@@ -374,7 +374,9 @@ size_t sq_squeezenet_workspace_bytes(int N);
  *   sq_squeezenet_forward_packed(): sq_squeezenet_forward without the per-call kernel
  *     transform (SQ_F32), or sq_squeezenet_forward_bf16 on an fp32 image (SQ_BF16); `packed`
  *     must have been written for the mode in force and is only read.  Workspace and taps as
- *     for sq_squeezenet_forward.
+ *     for sq_squeezenet_forward.  SQ_F32: the same result as sq_squeezenet_forward up to rounding
+ *     (from ten images on, without taps, layers run on the f16 matrix instructions with each fp32
+ *     operand split into two f16 values; otherwise bit for bit).
  * Errors: SQ_ERR_NULL, SQ_ERR_SHAPE, SQ_ERR_WORKSPACE (packed misaligned or too small),
  * SQ_ERR_UNSUPPORTED (unknown dtype, batch too large), SQ_ERR_HIP.
  */
