@@ -297,6 +297,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
     }
     const int pp = 32 * qblk + j, ppc = POOL ? min(pp, 55) : 0;
     f32x16 sum;                      // of the squeeze
+    float plain[8];                  // SPLIT: and, without its scale, what steps with an infinity or NaN add to it
     int sq_e = 127;                  // SPLIT: exponent of this pixel's scale, and the magnitude up to which it serves
     uint32_t sq_limit = 0;
     // 56 pooled pixels x 8 groups of four layers of a block, one per thread
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
 #pragma unroll
                         for (int r = 0; r < 8; ++r) {
                             const int m = 8 * (r >> 2) + 4 * h + (r & 3);
-                            sum[r] += __builtin_amdgcn_ldexpf(u * (m < p.Csq ? p.wsq32[m * 96 + cb * 32 + c] : 0.f), sq_e + sbq[m].x);
+                            plain[r] = __builtin_fmaf(u, m < p.Csq ? p.wsq32[m * 96 + cb * 32 + c] : 0.f, plain[r]);
                         }
                     }
                     return;
@@ -435,6 +436,8 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
             if (squeezer) {
 #pragma unroll
                 for (int k = 0; k < 16; ++k) sum[k] = SPLIT ? 0.f : __builtin_bit_cast(float, sbq[8 * (k >> 2) + 4 * h + (k & 3)].y);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) plain[k] = 0.f;
                 sq_e = 127;
                 sq_limit = 0;
             }
@@ -501,7 +504,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
                     if (8 * q < p.Csq) {
                         f32x4 v;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_ldexpf(sum[4 * q + i], -sq_e - sbq[8 * q + 4 * h + i].x);
+                        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_ldexpf(sum[4 * q + i], -sq_e - sbq[8 * q + 4 * h + i].x) + plain[4 * q + i];
                         parts[(wv * 2 + q) * 64 + lane] = v;
                     }
                 last_tile = tile;

@@ -215,3 +215,40 @@ def test_classifier_on_split_operands(sq, n, cin, h, w, cout, taken):
     np.testing.assert_array_equal(np.isinf(odd), np.isinf(want))
     keep = np.isfinite(want) & (np.arange(n) != 4)[:, None]
     assert (np.abs(odd - ref)[keep & (np.arange(n) != 3)[:, None]] <= ((cin + h * w + 16) * 2.0 ** -24 * terms)[keep & (np.arange(n) != 3)[:, None]]).all()
+
+
+def network_of_single_layers(sq, x, params):
+    """The network as single calls of the kernels that take every shape, each a plain fp32 sum per output element."""
+    conv = lambda t, i, stride=1, pad=0, **kw: sq.sq_conv2d_forward_ex(t, params[i], params[i + 1], stride, pad, True, algo=sq.SQ_ALGO_DIRECT, **kw)
+    t = sq.sq_maxpool(conv(x, 0, 2, 2), 3, 2)
+    for f in range(8):
+        s = conv(t, 2 + 6 * f)
+        ce = params[4 + 6 * f].shape[0]
+        t = torch.empty((s.shape[0], 2 * ce, *s.shape[2:]), device="cuda")
+        conv(s, 4 + 6 * f, out=t, c_offset=0)
+        conv(s, 6 + 6 * f, 1, 1, out=t, c_offset=ce)
+        if f in (2, 6):
+            t = sq.sq_maxpool(t, 3, 2)
+    return sq.sq_softmax(sq.sq_avgpool_global(conv(t, 50)))
+
+
+@pytest.mark.parametrize("where", ["image", "conv1 kernels", "squeeze kernels"])
+def test_one_launch_first_layers_with_infinities_and_nan(sq, where):
+    """An infinity or NaN reaches the results that fp32 sums carry it to and no others: maxima and ReLU drop a NaN."""
+    n = 10
+    cfg = synth.config_squeezenet(seed=77, n=n)
+    x, params = cfg["x"].copy(), [p.copy() for p in cfg["params"]]
+    if where == "image":
+        x[0, 1, 100, 57], x[3, 2, 7, 200], x[3, 0, 150, 3] = np.inf, -np.inf, np.nan
+    elif where == "conv1 kernels":
+        params[0][17, 1, 3, 4], params[0][90, 0, 2, 5] = np.nan, -np.inf     # (taps that no padding meets)
+    else:
+        params[2][5, 40], params[2][11, 3] = np.nan, -np.inf
+    xd, pd = dev(x), [dev(p) for p in params]
+    sq.sq_profile_begin(64)
+    got = sq.sq_squeezenet_forward_packed(xd, pd, sq.sq_pack_weights(pd, sq.SQ_F32))
+    assert any("k7s2c3_split+pool3s2+k1" in r["name"] for r in sq.sq_profile_end())
+    pick = [0, 3, 9]
+    want = network_of_single_layers(sq, xd[pick].contiguous(), pd).cpu().numpy()
+    assert np.isfinite(want).all()
+    assert_close(got[pick].cpu().numpy(), want, where)
