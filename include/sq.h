@@ -164,11 +164,14 @@ int sq_conv2d_forward_ex(const void *in, const void *w, const float *b, float *o
  *     fits the shape can run; a smaller one only rules those algorithms out.
  *     Contents on return are unspecified; the same scratch must not be used by
  *     two calls in flight at once.
- *   fp32 layers of 3x3 and 5x5 kernels, stride 1 and pad (K-1)/2 run on the f16 matrix
- *   instructions when the scratch is given, every operand as the sum of two f16 values with
- *   scales that are powers of two and fp32 sums: no less exact than the fp32 instructions
- *   (values 2^17 and more below the largest of a neighbourhood are added up in a pass of
- *   their own); infinities and NaN give undefined results where a window touches them.
+ *   fp32 layers of 3x3 and 5x5 kernels, stride 1 and pad (K-1)/2 can run on the f16 matrix
+ *     instructions when the scratch is given, every operand as the sum of two f16 values (23
+ *     bits of it at least) with scales that are powers of two, and fp32 sums.  The error of a
+ *     result stays within what fp32 sums of its own terms may show, whatever larger values lie
+ *     beside them: where operands are too far apart for one scale, and where an infinity or NaN
+ *     may reach, sums are made on the fp32 instructions.  The same holds for the other entry
+ *     points that use such operands: sq_conv2d_forward of 7x7 layers of stride 2 with three
+ *     input layers, sq_fire_forward and its packed form, sq_classifier_forward, and the fp32 network.
  *   A layer with stride S >= 2 can also run as a stride-1 convolution of a
  *     space-to-depth copy of its input (S*S times the input layers, kernels of
  *     ceil(K/S) x ceil(K/S)), which the library makes in the workspace; under

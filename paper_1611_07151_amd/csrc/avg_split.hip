@@ -21,7 +21,7 @@ constexpr int kPix = 96;                   // pixels of a tile
 
 struct AvgParams {
     const float *in;          // fp32 map [N][Cin][HW]
-    const u32x4 *wk;          // kernels from split_kernels(), their scales' exponents, bias or nullptr, the kernels as given
+    const u32x4 *wk;          // kernels from split_kernels(), their layers' words, bias or nullptr, the kernels as given
     const int *sk;
     const float *b, *raw;
     float *sums;              // [tiles][slots][Cout]: plane sums of the images a tile touches
@@ -38,7 +38,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
     constexpr int plane = CK / 8 * kPix;
     __shared__ u32x4 patch[2 * plane];                        // [hi, lo][CK / 8][96][8 layers]
     __shared__ uint32_t top[kPix];                            // largest magnitude of a pixel so far
-    __shared__ int odd;                                       // an infinity or NaN among them
+    __shared__ int marks;                                     // 1: an infinity or NaN among them, 2: a pixel's layers are spread wide
 
     const int t = threadIdx.x, lane = t & 63, j = lane & 31, h = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -63,25 +63,27 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
         off[k] = gp < p.PT ? (uint32_t)((n * p.Cin + cb * 8) * p.HW + gp - n * p.HW) * 4u : kOob;
     }
     float v[PER][8];
-    f32x16 acc[3];
+    Range range[PER];                                         // of the layers a thread has staged of its pixels
+    f32x16 main[3], cross[3];
     int es[3] = {127, 127, 127};
 #pragma unroll
     for (int pb = 0; pb < 3; ++pb)
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc[pb][k] = 0.f;
+        for (int k = 0; k < 16; ++k) main[pb][k] = cross[pb][k] = 0.f;
     // the layers in v: scales, sums of the layers before to the new scale, patch
     auto stage = [&]() {
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            const uint32_t m = magnitude8(v[k]);
-            if (odd8(v[k])) odd = 1;
-            atomicMax(&top[q[k]], m);
+            range[k].add8(v[k]);
+            atomicMax(&top[q[k]], range[k].top_bits());
         }
         __syncthreads();                   // (nobody reads the patch any more either)
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             u32x4 hi, lo;
-            split8(v[k], pow2(scale_exponent(top[q[k]])), hi, lo);
+            const uint32_t m = top[q[k]];
+            if (m >= kOddMagnitude || spread(m, range[k].low)) atomicOr(&marks, m >= kOddMagnitude ? 1 : 2);
+            split8(v[k], pow2(scale_exponent(m)), hi, lo);
             patch[t + k * NT] = hi;
             patch[t + k * NT + plane] = lo;
         }
@@ -90,7 +92,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
             const int e = scale_exponent(top[pb * 32 + j]);
             if (__ballot(e != es[pb])) {
 #pragma unroll
-                for (int k = 0; k < 16; ++k) acc[pb][k] = __builtin_amdgcn_ldexpf(acc[pb][k], e - es[pb]);
+                for (int k = 0; k < 16; ++k) {
+                    main[pb][k] = __builtin_amdgcn_ldexpf(main[pb][k], e - es[pb]);
+                    cross[pb][k] = __builtin_amdgcn_ldexpf(cross[pb][k], e - es[pb]);
+                }
                 es[pb] = e;
             }
         }
@@ -99,7 +104,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
 #pragma unroll
     for (int k = 0; k < PER * 8; ++k) v[k >> 3][k & 7] = buf_ld(rin, off[k >> 3], (uint32_t)((k & 7) * p.HW) * 4u);
     if (t < kPix) top[t] = 0;
-    if (t == 0) odd = 0;
+    if (t == 0) marks = 0;
     __syncthreads();
     stage();
     // Steps of 16 layers: pixels are read one step ahead, kernels D steps, and a step asks for its share of the next layers
@@ -121,11 +126,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
             __builtin_amdgcn_sched_barrier(0);
             const u32x4 (&b)[3][2] = bt[s & 1];
 #pragma unroll
-            for (int pb = 0; pb < 3; ++pb) acc[pb] = mma(a[s % D][1], b[pb][0], acc[pb]);
+            for (int pb = 0; pb < 3; ++pb) cross[pb] = mma(a[s % D][1], b[pb][0], cross[pb]);
 #pragma unroll
-            for (int pb = 0; pb < 3; ++pb) acc[pb] = mma(a[s % D][0], b[pb][1], acc[pb]);
+            for (int pb = 0; pb < 3; ++pb) main[pb] = mma(a[s % D][0], b[pb][0], main[pb]);
 #pragma unroll
-            for (int pb = 0; pb < 3; ++pb) acc[pb] = mma(a[s % D][0], b[pb][0], acc[pb]);
+            for (int pb = 0; pb < 3; ++pb) cross[pb] = mma(a[s % D][0], b[pb][1], cross[pb]);
             __builtin_amdgcn_sched_barrier(0);
             const int ahead = s + D < STEPS || more ? s + D : s;      // (the last steps read themselves again)
             a[s % D][0] = w[ahead * 128];
@@ -140,39 +145,51 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
     }
 
     // ---- scales, bias, ReLU; register 4q + i = layer 8q + 4h + i
-    const int ml = mb * 32 + 4 * h;
-    int ex[16];
+    const int ml = mb * 32 + 4 * h, mj = mb * 32 + j;
+    int word[16];
     float bias[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         const int m = min(ml + 8 * (k >> 2) + (k & 3), p.Cout - 1);
-        ex[k] = p.sk[m];
+        word[k] = p.sk[m];
         bias[k] = p.b ? p.b[m] : 0.f;
     }
-    bool plain = odd;
+    int odd = marks & 1, wide = marks & 2;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) plain |= ex[k] == kPlainRow;
-    if (__ballot(plain)) {                // an infinity or NaN: in fp32 from memory
+    for (int k = 0; k < 16; ++k) {
+        odd |= word[k] & kOddRow;
+        wide |= word[k] & kWideRow;
+    }
+    // on the fp32 instructions from memory: an infinity or NaN, or sums too small for operands that are spread wide
+    bool again = __ballot(odd) != 0;
+    if (!again && __ballot(wide)) {
+        float least = kSmall;
 #pragma unroll
-        for (int pb = 0; pb < 3; ++pb) {
-            const int gp = min(p0 + pb * 32 + j, p.PT - 1), n = fdiv(gp, p.dHW);
-            const float *x = p.in + (size_t)n * p.Cin * p.HW + gp - n * p.HW;
+        for (int pb = 0; pb < 3; ++pb)
 #pragma unroll
-            for (int k = 0; k < 16; ++k) acc[pb][k] = 0.f;
-#pragma unroll 1
-            for (int c = 0; c < p.Cin; ++c)
-#pragma unroll
-                for (int k = 0; k < 16; ++k)
-                    acc[pb][k] = __builtin_fmaf(x[(size_t)c * p.HW], p.raw[(size_t)min(ml + 8 * (k >> 2) + (k & 3), p.Cout - 1) * p.Cin + c], acc[pb][k]);
-            es[pb] = 0;
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) ex[k] = 0;
+            for (int k = 0; k < 16; ++k) least = fminf(least, ml + 8 * (k >> 2) + (k & 3) < p.Cout ? fabsf(main[pb][k]) : kSmall);
+        again = __ballot(least < kSmall) != 0;
     }
 #pragma unroll
     for (int pb = 0; pb < 3; ++pb)
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc[pb][k] = fmaxf(__builtin_amdgcn_ldexpf(acc[pb][k], -es[pb] - ex[k]) + bias[k], 0.f);
+        for (int k = 0; k < 16; ++k) main[pb][k] = joined(main[pb][k], cross[pb][k]);
+    if (again) {
+        const rsrc_t rw = make_rsrc(p.raw, (uint32_t)(p.Cout * p.Cin) * 4u);
+#pragma unroll
+        for (int pb = 0; pb < 3; ++pb) {
+            const int gp = p0 + pb * 32 + j, n = fdiv(gp, p.dHW);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) main[pb][k] = 0.f;
+            main[pb] = plain_tap(main[pb], rw, mj < p.Cout ? (uint32_t)(mj * p.Cin + h) * 4u : kOob, 4u, rin,
+                                 gp < p.PT ? (uint32_t)((n * p.Cin + h) * p.HW + gp - n * p.HW) * 4u : kOob, 4u * p.HW, p.Cin, h);
+        }
+    }
+#pragma unroll
+    for (int pb = 0; pb < 3; ++pb)
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            main[pb][k] = fmaxf(__builtin_amdgcn_ldexpf(main[pb][k], again ? 0 : -es[pb] - row_exponent(word[k])) + bias[k], 0.f);
 
     // ---- plane sums per image: over a lane's three pixels, then over 32 lanes
     const int first = fdiv(p0, p.dHW), last = fdiv(min(p0 + kPix, p.PT) - 1, p.dHW);
@@ -188,7 +205,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
         for (int k = 0; k < 16; ++k) {
             float s = 0.f;
 #pragma unroll
-            for (int pb = 0; pb < 3; ++pb) s += image[pb] == n ? acc[pb][k] : 0.f;
+            for (int pb = 0; pb < 3; ++pb) s += image[pb] == n ? main[pb][k] : 0.f;
             s = half_wave_sum(s);
             const int m = ml + 8 * (k >> 2) + (k & 3);
             if (j == 31 && mine && m < p.Cout) row[m] = s;

@@ -1,16 +1,20 @@
 // fp32 contractions on the f16 matrix instructions (internal).
 //
-// An fp32 value scaled by a power of two into the upper part of the f16 range is the sum of two f16 values, hi + lo,
-// up to 2^-24 of itself (hi rounded to nearest leaves 12 bits and a sign, lo keeps 11 of them).  A product of two such
-// sums is hi*hi + hi*lo + lo*hi; the dropped lo*lo is below 2^-24 of it.  So three v_mfma_f32_32x32x16_f16 with fp32
-// accumulation do the work of eight v_mfma_f32_32x32x2_f32: 96 against 512 cycles of a SIMD's matrix unit.  Measured
-// on uniform and normal operands, relative 2-norm error against 64-bit sums, this form / the fp32 instructions:
-// 1.2e-7 / 1.2e-7 at 96 terms, 3.0e-7 / 3.3e-7 at 576, 5.3e-7 / 5.9e-7 at 2304 (one accumulator; with the two cross
-// terms in an accumulator of their own, as here, the sum is rounded a third as often).
+// An fp32 value scaled by a power of two into the upper part of the f16 range is hi + lo / 2^11, both f16: hi rounded to
+// nearest leaves a remainder of at most 2^-11 of the value's binade, of which lo keeps 11 bits.  Three quarters of all fp32
+// values are held exactly, the others up to their last bit, 2^-23 of the value at most.  A product of two such sums is
+// hi*hi + (hi*lo + lo*hi) / 2^11; the dropped lo*lo is at most 2^-22 of it, 2^-24 as a rule.  So three
+// v_mfma_f32_32x32x16_f16 with fp32 accumulation, the cross terms in an accumulator of their own, do the work of eight
+// v_mfma_f32_32x32x2_f32: 96 against 512 cycles of a SIMD's matrix unit.  What the operands lose is less than what the
+// fp32 instructions lose in their longer chain of additions (16 terms are added per rounding instead of two).
 //
 // Scales are powers of two, so applying and removing them is exact: kernels get one per output layer, activations one
-// per pixel tile or pixel, chosen from the largest magnitude there.  f16 holds 2^-24 .. 2^15, so values down to 2^-17
-// of the scale's reference keep all their bits and smaller ones an absolute error of 2^-40 of it.
+// per pixel tile or pixel, chosen from the largest magnitude there, which comes to lie in [2^13, 2^14).  lo ends at 2^-24,
+// that is 2^-35 of hi's units: values from 2^-25 of the largest on keep all their bits, smaller ones are held to an
+// absolute 2^-36 (2^-49 of the largest).  That is no loss to a sum that a larger term reaches, but it is where the larger
+// ones meet zeros.  So tiles and output layers with a non-zero value below 2^-25 of their largest are marked (kWide), and of
+// their sums those that stay below kSmall (2^-20 of one large product and less: what the operands lose is then no longer
+// far below the sum) are made again on the fp32 instructions, from memory, as are all that an infinity or NaN may reach.
 #pragma once
 
 #include "conv_mfma_common.h"
@@ -25,36 +29,37 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_a4 __attribute__((aligned(4)));   // four floats at any fp32 address
 
-// An infinity or NaN has no hi and lo: sums that it may reach are made from the fp32 operands instead.
-__device__ __forceinline__ bool odd8(const float *v)
-{
-    uint32_t m = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m = max(m, __builtin_bit_cast(uint32_t, v[k]) & 0x7fffffffu);
-    return m >= 0x7f800000u;
-}
-constexpr int kPlainRow = 1 << 30;    // in the place of a scale's exponent: an output layer whose kernels hold such a value
-// Magnitude bits of a finite value; infinities and NaN count as zero, so that they do not set a scale.
-__device__ __forceinline__ uint32_t magnitude(float v)
-{
-    const uint32_t m = __builtin_bit_cast(uint32_t, v) & 0x7fffffffu;
-    return m >= 0x7f800000u ? 0u : m;
-}
-// The largest magnitude of eight values (the exact rule for infinities and NaN only where one is there).
-__device__ __forceinline__ uint32_t magnitude8(const float *v)
-{
-    uint32_t m = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m = max(m, __builtin_bit_cast(uint32_t, v[k]) & 0x7fffffffu);
-    if (__ballot(m >= 0x7f800000u)) {
-        m = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) m = max(m, magnitude(v[k]));
+constexpr int kLowBits = 11;                       // lo is kept times 2^11
+constexpr uint32_t kWide = 25u << 23;              // spread of magnitudes (as bits) up to which every value keeps its bits
+constexpr float kSmall = 64.f;                     // sums of marked tiles and layers below this, scales included, are made again
+// Range of the magnitudes of a set of values: the largest (NaN if one is), and the smallest but zero as twice its bits less
+// one (~0 if there is none).  Two instructions per value.
+struct Range {
+    float top = 0.f;
+    uint32_t low = ~0u;
+    __device__ __forceinline__ void add2(float a, float b)
+    {
+        top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top, fabsf(a)), fabsf(b));
+        low = min(low, min((__builtin_bit_cast(uint32_t, a) << 1) - 1u, (__builtin_bit_cast(uint32_t, b) << 1) - 1u));
     }
-    return m;
+    __device__ __forceinline__ void add8(const float *v)
+    {
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) add2(v[k], v[k + 1]);
+    }
+    __device__ __forceinline__ uint32_t top_bits() const { return __builtin_bit_cast(uint32_t, top) & 0x7fffffffu; }
+};
+constexpr uint32_t kOddMagnitude = 0x7f800000u;      // bits of an infinity; above: NaN
+__device__ __forceinline__ bool spread(uint32_t top_bits, uint32_t low) { return top_bits > (low >> 1) && top_bits - (low >> 1) >= kWide; }
+// An output layer's scale and marks in one word: the exponent in the lower 16 bits, and
+constexpr int kWideRow = 1 << 16, kOddRow = 1 << 17;      // its kernels are spread wide / hold an infinity or NaN
+__device__ __forceinline__ int row_exponent(int row) { return (int)(short)row; }
+__device__ __forceinline__ int row_word(int exponent, uint32_t top, uint32_t low)
+{
+    return (exponent & 0xffff) | (spread(top, low) ? kWideRow : 0) | (top >= kOddMagnitude ? kOddRow : 0);
 }
 // Exponent of the power of two that brings a magnitude (bits) into [2^13, 2^14), one factor of two of room below 2^15;
-// 127 at most (zero and the smallest values).  Scales are kept as exponents: they are removed with ldexp, which neither
+// 127 at most (zero and the smallest values: their last bits lie above 2^-36 all the same).  Scales are kept as exponents: they are removed with ldexp, which neither
 // over- nor underflows on the way where the product of two powers of two would.
 __device__ __forceinline__ int scale_exponent(uint32_t mag) { return min(140 - (int)(mag >> 23), 127); }
 __device__ __forceinline__ float pow2(int e) { return __builtin_bit_cast(float, (uint32_t)(e + 127) << 23); }   // -126 .. 127
@@ -79,12 +84,13 @@ __device__ __forceinline__ float half_wave_sum(float v)
     return v;
 }
 
-// Two values as hi and lo pairs: one packed conversion, two subtractions that round to f16.
+// Two values as hi and lo pairs.
 __device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo)
 {
     asm volatile("" : "+v"(a), "+v"(b));     // (else the scaling is folded into three instructions per value instead of one)
+    constexpr float up = 1 << kLowBits;
     const f16x2 h = {(_Float16)a, (_Float16)b};
-    const f16x2 l = {(_Float16)(a - (float)h.x), (_Float16)(b - (float)h.y)};
+    const f16x2 l = {(_Float16)((a - (float)h.x) * up), (_Float16)((b - (float)h.y) * up)};
     hi = __builtin_bit_cast(uint32_t, h);
     lo = __builtin_bit_cast(uint32_t, l);
 }
@@ -101,6 +107,30 @@ __device__ __forceinline__ void split8(const float *v, float s, u32x4 &hi, u32x4
 __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+
+// hi*hi and the cross terms as one sum
+__device__ __forceinline__ float joined(float main, float cross) { return __builtin_fmaf(cross, 1.f / (1 << kLowBits), main); }
+
+// Adds, on the fp32 matrix instructions, the products of one kernel tap: 32 output layers (lane j of either half: a layer)
+// x 32 pixels (lane j: a pixel) over Cin input layers, two at a time (half h: the second).  w_at and x_at are the lane's byte
+// offsets of layer h, or kOob for layers and pixels that are not there; the steps are the bytes between input layers.
+// Straight from memory, about ten times the time of the split form.
+__device__ __forceinline__ f32x16 plain_tap(f32x16 acc, rsrc_t rw, uint32_t w_at, uint32_t w_step, rsrc_t rx, uint32_t x_at, uint32_t x_step, int Cin, int h)
+{
+    for (int c0 = 0; c0 < Cin; c0 += 8) {
+        float w[4], x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t c = (uint32_t)(c0 + 2 * k);
+            const bool there = (int)c + h < Cin;
+            w[k] = buf_ld(rw, there ? w_at : kOob, c * w_step);
+            x[k] = buf_ld(rx, there ? x_at : kOob, c * x_step);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc = Mfma<32>::run(w[k], x[k], acc);
+    }
+    return acc;
 }
 
 }  // namespace split

@@ -10,13 +10,13 @@ namespace split {
 
 // Kernels [Cout][Cin][K][K] fp32 -> operand order [Cout/32][Cin/16][K*K][hi, lo][64 lanes][8 f16] (lane l: output layer
 // 32*mb + l % 32, input layers 16*g + 8*(l/32) .. +7; layers that do not exist are zero), scaled per output layer;
-// then the scales' exponents, one int per output layer (padded to 32).  One workgroup per output layer; its row goes
+// then a word per output layer (padded to 32): its scale's exponent and marks (row_word).  One workgroup per output layer; its row goes
 // through LDS where it fits (row_in_lds floats), so that memory sees whole lines read and 16 bytes per store.
 constexpr int kSplitLayers = 9;
 struct SplitLayer {
     const float *w;
     u32x4 *wp;
-    int *exponents;
+    int *words;
     int Cout, Cin, KK, G;
     FastDiv dKK;
 };
@@ -28,38 +28,39 @@ struct SplitList {
 __global__ __launch_bounds__(256) void split_kernels_kernel(const SplitList list)
 {
     extern __shared__ float row_lds[];
-    __shared__ uint32_t top, odd;
+    __shared__ uint32_t top, low;
     int l = 0;
     while ((int)blockIdx.x >= list.first[l + 1]) ++l;
     const SplitLayer &y = list.layer[l];
     const float *const w = y.w;
     u32x4 *const wp = y.wp;
-    int *const exponents = y.exponents;
+    int *const words = y.words;
     const int Cout = y.Cout, Cin = y.Cin, KK = y.KK, G = y.G, row_in_lds = list.row_in_lds;
     const FastDiv dKK = y.dKK;
     const int m = (int)blockIdx.x - list.first[l], n = Cin * KK;
     const float *row = w + (size_t)m * n;
-    if (threadIdx.x == 0) top = odd = 0;
+    if (threadIdx.x == 0) { top = 0; low = ~0u; }
     __syncthreads();
-    uint32_t mx = 0;
+    Range range;
     if (m < Cout)
         for (int e0 = threadIdx.x; e0 < n; e0 += 256 * 8) {
             float v[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = e0 + 256 * k < n ? row[e0 + 256 * k] : 0.f;
-            if (odd8(v)) odd = 1;
+            range.add8(v);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                mx = max(mx, magnitude(v[k]));
+            for (int k = 0; k < 8; ++k)
                 if (e0 + 256 * k < row_in_lds) row_lds[e0 + 256 * k] = v[k];
-            }
         }
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) atomicMax(&top, mx);
+    const uint32_t mx = wave_max(range.top_bits()), mn = wave_min(range.low);
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(&top, mx);
+        atomicMin(&low, mn);
+    }
     __syncthreads();
     const int ex = scale_exponent(top);
     const float s = pow2(ex);
-    if (threadIdx.x == 0) exponents[m] = odd ? kPlainRow : ex;
+    if (threadIdx.x == 0) words[m] = row_word(ex, top, low);
     for (int e = threadIdx.x; e < G * 2 * KK; e += 256) {
         const int c8 = fdiv(e, dKK), tap = e - c8 * KK;
         float v[8];
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(256) void split_kernels_kernel(const SplitList list
 struct ExpandParams {
     const float *in;          // fp32 map [N][Cin][H][W]
     float *out;               // fp32 [N][ldc][H][W]
-    const u32x4 *wk;          // K x K kernels from split_kernels_kernel, their scales' exponents, bias or nullptr
+    const u32x4 *wk;          // K x K kernels from split_kernels_kernel, their layers' words, bias or nullptr
     const int *sk;
     const float *bk;
     const float *raw;         // the K x K kernels as given
@@ -164,10 +165,9 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     u32x4 *const patch = reinterpret_cast<u32x4 *>(smem);
     const int plane = (p.CK >> 3) * p.TP;
-    int *const rows = reinterpret_cast<int *>(patch + p.patch_elems);            // [8 wavefronts][32] scales' exponents of a 1x1 block
-    uint32_t *const red = reinterpret_cast<uint32_t *>(rows + 8 * 32);           // [8 wavefronts][2], whether the patch holds an infinity or NaN, -
-    uint32_t *const pixel_top = red + 18;                                        // [TP, even] largest magnitude of a pixel
-    int2 *const bias = reinterpret_cast<int2 *>(pixel_top + ((p.TP + 1) & ~1));  // [units][cwn][32] (scale's exponent, bias)
+    int *const rows = reinterpret_cast<int *>(patch + p.patch_elems);            // [8 wavefronts][32] words of a 1x1 block's layers
+    uint32_t *const red = reinterpret_cast<uint32_t *>(rows + 8 * 32);           // [8 wavefronts][2] range of the magnitudes
+    int2 *const bias = reinterpret_cast<int2 *>(red + 16);                       // [units][cwn][32] (layer's word, bias)
 
     const int t = threadIdx.x, lane = t & 63, nthreads = (int)blockDim.x;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6), waves = nthreads >> 6;
@@ -221,41 +221,30 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = ok && c + k < p.Cin ? src[(size_t)k * p.HW] : 0.f;
     };
-    auto top_of = [&](const float (&v)[8]) { return magnitude8(v); };
-    // largest and smallest over the workgroup
-    auto reduce = [&](uint32_t &mx, uint32_t &mn) {
-        mx = wave_max(mx);
-        mn = wave_min(mn);
-        __syncthreads();
-        if (lane == 0) { red[2 * wv] = mx; red[2 * wv + 1] = mn; }
-        __syncthreads();
-        for (int k = 0; k < waves; ++k) { mx = max(mx, red[2 * k]); mn = min(mn, red[2 * k + 1]); }
-        mx = __builtin_amdgcn_readfirstlane(mx);
-        mn = __builtin_amdgcn_readfirstlane(mn);
-    };
-
-    // ---- range of the magnitudes of the patch: the largest of each pixel that is not zero throughout, over the pixels.
-    // (Per pixel, not per value: small values beside larger ones of the same pixel are no loss to any sum, and a pixel
-    // whose layers are all below 2^-17 of the patch's largest, but not all zero, is rare enough in the results of a ReLU
-    // that its tile may take several times as long.)
-    constexpr uint32_t kWindow = 17u << 23;
+    // ---- the patch, and the range of the magnitudes it holds
     const int items = (p.CK >> 3) * p.TP;
     constexpr int kKeep = PARTS ? 0 : 10;                      // elements a thread holds from the scan to the split
-    uint32_t mx = 0, mn = 0xffffffffu;
-    bool one_window;
-    auto pixel_of = [&](int e) { return e - fdiv(e, p.dTP) * p.TP; };
+    uint32_t mx, mn;
     auto put = [&](int e, const float (&v)[8], float s) {
         u32x4 hi, lo;
         split8(v, s, hi, lo);
         patch[e] = hi;
         patch[e + plane] = lo;
     };
+    auto stage = [&](int e0, int c0, float s) {
+        for (int e = e0; e < items; e += nthreads) {
+            float v[8];
+            fetch(e, c0, v);
+            put(e, v, s);
+        }
+    };
     {
         float kept[kKeep + 1][8];
+        Range range;
 #pragma unroll
         for (int k = 0; k < kKeep; ++k)
             if (t + k * nthreads < items) fetch(t + k * nthreads, 0, kept[k]);
-        // scales and bias of this workgroup's layers (the 1x1 kernels' scales are found with the kernels)
+        // words and bias of this workgroup's layers (those of the 1x1 kernels are found with the kernels)
         for (int e = t; e < (uk + u1) * p.cwn * 32; e += nthreads) {
             const int u = e / (p.cwn * 32), c = (e >> 5) - u * p.cwn;
             const bool one = u >= uk;
@@ -263,60 +252,33 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
             const float *b = one ? p.b1 : p.bk;
             bias[e] = int2{!one && m < p.Cout ? p.sk[m] : 0, b && m < (one ? p.Cout1 : p.Cout) ? __builtin_bit_cast(int, b[m]) : 0};
         }
-        for (int e = t; e < p.TP; e += nthreads) pixel_top[e] = 0;
-        if (t == 0) red[16] = 0;
-        __syncthreads();
-        auto scan = [&](int e, const float (&v)[8]) {
-            const uint32_t m = top_of(v);
-            if (odd8(v)) red[16] = 1;
-            if (m) atomicMax(&pixel_top[pixel_of(e)], m);
-        };
 #pragma unroll
         for (int k = 0; k < kKeep; ++k)
-            if (t + k * nthreads < items) scan(t + k * nthreads, kept[k]);
+            if (t + k * nthreads < items) range.add8(kept[k]);
         for (int c0 = 0; c0 < p.Cin; c0 += p.CK)
             for (int e = t + kKeep * nthreads; e < items; e += nthreads) {
                 float v[8];
                 fetch(e, c0, v);
-                scan(e, v);
+                range.add8(v);
             }
+        mx = wave_max(range.top_bits());
+        mn = wave_min(range.low);
+        if (lane == 0) { red[2 * wv] = mx; red[2 * wv + 1] = mn; }
         __syncthreads();
-        for (int e = t; e < p.TP; e += nthreads) {
-            const uint32_t m = pixel_top[e];
-            mx = max(mx, m);
-            if (m) mn = min(mn, m);
-        }
-        reduce(mx, mn);
-        one_window = mx == 0 || mx - mn < kWindow;
-        if (!PARTS && one_window) {
+        for (int k = 0; k < waves; ++k) { mx = max(mx, red[2 * k]); mn = min(mn, red[2 * k + 1]); }
+        mx = __builtin_amdgcn_readfirstlane(mx);
+        mn = __builtin_amdgcn_readfirstlane(mn);
+        if (!PARTS) {
             const float s = pow2(scale_exponent(mx));
 #pragma unroll
             for (int k = 0; k < kKeep; ++k)
                 if (t + k * nthreads < items) put(t + k * nthreads, kept[k], s);
-            for (int e = t + kKeep * nthreads; e < items; e += nthreads) {
-                float v[8];
-                fetch(e, 0, v);
-                put(e, v, s);
-            }
+            stage(t + kKeep * nthreads, 0, s);
             __syncthreads();
         }
     }
-    // splits, with scale s, the pixels whose largest magnitude lies in the window [lo, lo + 2^17)
-    auto stage = [&](int c0, float s, uint32_t lo) {
-        for (int e = t; e < items; e += nthreads) {
-            float v[8];
-            fetch(e, c0, v);
-            if (!one_window) {
-                const uint32_t m = pixel_top[pixel_of(e)];
-                if (m < lo || m - lo >= kWindow) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        if (magnitude(v[k])) v[k] = 0.f;      // (infinities and NaN stay)
-                }
-            }
-            put(e, v, s);
-        }
-    };
+    const int es = scale_exponent(mx);
+    const bool odd = mx >= kOddMagnitude, wide = spread(mx, mn);
 
     // ---- this wavefront's pixels
     int lane_pix[PB];
@@ -332,12 +294,11 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
     const rsrc_t rout = make_rsrc(p.out, (uint32_t)((size_t)p.N * p.ldc * p.HW * 4));
     const float lowest = p.relu ? 0.f : -__builtin_inff();
 
-    // ---- a block in fp32 from memory, for layers and patches with an infinity or NaN
-    const bool odd_patch = __builtin_amdgcn_readfirstlane(red[16]) != 0;
+    // ---- a block of 32 output layers on the fp32 instructions, from memory
     auto plain = [&](const float *w, int taps, int mb, int Cout, int coff, const int2 *sb) {
-        const int reach = taps == 1 ? 0 : p.P, side = 2 * reach + 1;
-        const rsrc_t rw = make_rsrc(w, (uint32_t)(Cout * p.Cin * taps) * 4u);       // (layers past the last read zeros)
-        const uint32_t row = (uint32_t)(p.Cin * taps) * 4u, wo = (uint32_t)(mb * 32 + 4 * h) * row;
+        const int side = taps == 1 ? 1 : K, reach = side / 2, m = mb * 32 + j;
+        const rsrc_t rw = make_rsrc(w, (uint32_t)(Cout * p.Cin * taps) * 4u), rx = make_rsrc(p.in, (uint32_t)((size_t)p.N * p.Cin * p.HW * 4));
+        const uint32_t wo = (uint32_t)((m * p.Cin + h) * taps) * 4u;
 #pragma unroll 1
         for (int pb = 0; pb < PB; ++pb) {
             const int gp = p0 + (grp * PB + pb) * 32 + j, gq = min(gp, p.PT - 1), n = fdiv(gq, p.dHW), pix = gq - n * p.HW, y = fdiv(pix, p.dW), x = pix - y * p.W;
@@ -345,27 +306,35 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
 #pragma unroll
             for (int k = 0; k < 16; ++k) sum[k] = 0.f;
 #pragma unroll 1
-            for (int c = 0; c < p.Cin; ++c)
-#pragma unroll 1
-                for (int tap = 0; tap < taps; ++tap) {
-                    const int yy = y + tap / side - reach, xx = x + tap % side - reach;
-                    const float v = yy >= 0 && yy < p.H && xx >= 0 && xx < p.W ? p.in[((size_t)n * p.Cin + c) * p.HW + yy * p.W + xx] : 0.f;
-#pragma unroll
-                    for (int k = 0; k < 16; ++k)
-                        sum[k] = __builtin_fmaf(v, buf_ld(rw, wo + (uint32_t)(c * taps + tap) * 4u, (uint32_t)(8 * (k >> 2) + (k & 3)) * row), sum[k]);
-                }
+            for (int tap = 0; tap < taps; ++tap) {
+                const int yy = y + tap / side - reach, xx = x + tap % side - reach;
+                const bool inside = yy >= 0 && yy < p.H && xx >= 0 && xx < p.W;
+                sum = plain_tap(sum, rw, m < Cout ? wo + 4u * tap : kOob, 4u * taps, rx, inside ? (uint32_t)((n * p.Cin + h) * p.HW + yy * p.W + xx) * 4u : kOob,
+                                4u * p.HW, p.Cin, h);
+            }
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
-                const int ml = 8 * (k >> 2) + 4 * h + (k & 3), m = mb * 32 + ml;
-                if (gp < p.PT && m < Cout) p.out[((size_t)n * p.ldc + coff + m) * p.HW + pix] = fmaxf(sum[k] + __builtin_bit_cast(float, sb[ml].y), lowest);
+                const int ml = 8 * (k >> 2) + 4 * h + (k & 3);
+                if (gp < p.PT && mb * 32 + ml < Cout)
+                    p.out[((size_t)n * p.ldc + coff + mb * 32 + ml) * p.HW + pix] = fmaxf(sum[k] + __builtin_bit_cast(float, sb[ml].y), lowest);
             }
         }
     };
 
     // ---- remove the scales, bias, ReLU; register 4q + i = layer 8q + 4h + i: 32 neighbouring pixels per store
-    auto finish = [&](f32x16 (&main)[PB], f32x16 (&cross)[PB], int es, int mb, int Cout, int coff, const int2 *sb, const int *scales,
-                      const float *w, int taps) {
-        if (odd_patch || __ballot((scales ? scales[j] : sb[j].x) == kPlainRow)) {
+    auto finish = [&](f32x16 (&main)[PB], f32x16 (&cross)[PB], int mb, int Cout, int coff, const int2 *sb, const int *words, const float *w, int taps) {
+        const int word = words ? words[j] : sb[j].x;
+        bool again = odd || __ballot(word & kOddRow);
+        if (!again && (wide || __ballot(word & kWideRow))) {
+            float least = kSmall;
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+                    least = fminf(least, mb * 32 + 8 * (k >> 2) + 4 * h + (k & 3) < Cout ? fabsf(main[pb][k]) : kSmall);
+            again = __ballot(least < kSmall) != 0;
+        }
+        if (again) {
             plain(w, taps, mb, Cout, coff, sb);
             return;
         }
@@ -375,11 +344,11 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
             for (int i = 0; i < 4; ++i) {
                 const int ml = 8 * q + 4 * h + i;
                 const int2 f = sb[ml];
-                const int ex = -es - (scales ? scales[ml] : f.x);
+                const int ex = -es - row_exponent(words ? words[ml] : f.x);
                 const uint32_t so = (uint32_t)((coff + mb * 32 + 8 * q + i) * p.HW) * 4u;
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
-                    const float v = fmaxf(__builtin_amdgcn_ldexpf(main[pb][4 * q + i] + cross[pb][4 * q + i], ex) + __builtin_bit_cast(float, f.y), lowest);
+                    const float v = fmaxf(__builtin_amdgcn_ldexpf(joined(main[pb][4 * q + i], cross[pb][4 * q + i]), ex) + __builtin_bit_cast(float, f.y), lowest);
                     buf_st(rout, mb * 32 + ml < Cout ? obase[pb] : kOob, so, v);
                 }
             }
@@ -390,159 +359,104 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
 #pragma unroll
             for (int k = 0; k < 16; ++k) main[pb][k] = cross[pb][k] = 0.f;
     };
-    // all windows of the patch's magnitudes in turn, smallest first (WIN), or the one there is: part(s, last) adds the
-    // contraction of what is staged with scale 2^s; returns that exponent for the sums
-    auto windows = [&](auto many, f32x16 (&main)[PB], f32x16 (&cross)[PB], auto part) -> int {
-        if constexpr (!decltype(many)::value) {
-            const int s = scale_exponent(mx);
-            part(s, 0u, true);
-            return s;
-        } else {
-            uint32_t lo = mn;
-            int s = 0, s_old = 1 << 20;
-            for (;;) {
-                uint32_t wmax = mx, next = 0xffffffffu;
-                if (mx - lo >= kWindow) {
-                    wmax = 0;
-                    for (int e = t; e < p.TP; e += nthreads) {
-                        const uint32_t m = pixel_top[e];
-                        if (m >= lo && m - lo < kWindow) wmax = max(wmax, m);
-                        if (m >= lo && m - lo >= kWindow) next = min(next, m);
-                    }
-                    reduce(wmax, next);
-                }
-                s = scale_exponent(wmax);
-                if (s_old != 1 << 20) {
-                    const int r = s - s_old;
-#pragma unroll
-                    for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) {
-                            main[pb][k] = __builtin_amdgcn_ldexpf(main[pb][k], r);
-                            cross[pb][k] = __builtin_amdgcn_ldexpf(cross[pb][k], r);
-                        }
-                }
-                part(s, lo, next == 0xffffffffu);
-                if (next == 0xffffffffu) return s;
-                s_old = s;
-                lo = next;
+    for (int u = 0; u < uk; ++u) {
+        const int mb = u * stride + first_block;
+        f32x16 main[PB], cross[PB];
+        clear(main, cross);
+        for (int c0 = 0; c0 < p.Cin; c0 += p.CK) {
+            if (PARTS) {
+                __syncthreads();
+                stage(t, c0, pow2(es));
+                __syncthreads();
             }
+            int g0, g1;
+            part(c0, g0, g1);
+            const bool more = c0 + p.CK < p.Cin;
+            const u32x4 *const nxt = stream(more || u + 1 == uk ? u : u + 1, more ? c0 + p.CK : 0);
+            contract<K, D, PB>(main, cross, a, stream(u, c0), nxt, g1 - g0, p.pitch, patch + 2 * g0 * p.TP, plane, p.TP, lane_pix, lane);
         }
-    };
-    auto run = [&](auto many) {
-        constexpr bool WIN = decltype(many)::value;
-        for (int u = 0; u < uk; ++u) {
+        // parts of the contraction: added up in the order of the parts, in the patch (nobody reads it any more: a launch that
+        // splits the contraction has one unit per wavefront)
+        if (p.kg > 1) {
+            f32x4 *const sums = reinterpret_cast<f32x4 *>(patch);
+            __syncthreads();
+            if (kw > 0) {
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        f32x4 v;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] = joined(main[pb][4 * q + i], cross[pb][4 * q + i]);
+                        sums[((wv * PB + pb) * 4 + q) * 64 + lane] = v;
+                    }
+            }
+            __syncthreads();
+            if (kw > 0) continue;
+            for (int k = 1; k < p.kg; ++k)
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 v = sums[(((wv + k) * PB + pb) * 4 + q) * 64 + lane];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) main[pb][4 * q + i] += v[i];
+                    }
+        }
+        if (mb < nbk) finish(main, cross, mb, p.Cout, p.coff, bias + (u * p.cwn + cw) * 32, nullptr, p.raw, K * K);
+    }
+    if constexpr (!PARTS) {
+        // 1x1 kernels straight from memory (at most 64 input layers): lane = output layer j, eight input layers per half; the
+        // loads of the next block are in flight while this one is multiplied and stored
+        f32x4 w[4][2];
+        auto load_w = [&](int u) {
+            const int m = min(u * stride + first_block, nb1 - 1) * 32 + j;
+            const float *const wr = p.w1 + (size_t)(m < p.Cout1 ? m : 0) * p.Cin + 8 * h;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float *const at = wr + 16 * (g < p.G ? g : 0);
+                w[g][0] = *reinterpret_cast<const f32x4_a4 *>(at);
+                w[g][1] = *reinterpret_cast<const f32x4_a4 *>(at + 4);
+            }
+        };
+        if (u1 > 0) load_w(0);
+        for (int u = 0; u < u1; ++u) {
             const int mb = u * stride + first_block;
+            Range range;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float v[8] = {w[g][0].x, w[g][0].y, w[g][0].z, w[g][0].w, w[g][1].x, w[g][1].y, w[g][1].z, w[g][1].w};
+                range.add8(v);
+            }
+            const uint32_t top = max(range.top_bits(), (uint32_t)__shfl_xor((int)range.top_bits(), 32, 64));
+            const uint32_t low = min(range.low, (uint32_t)__shfl_xor((int)range.low, 32, 64));
+            const int ex = scale_exponent(top);
+            const float ws = pow2(ex);
+            if (h == 0) rows[wv * 32 + j] = row_word(ex, top, low);
+            u32x4 ah[4], al[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float v[8] = {w[g][0].x, w[g][0].y, w[g][0].z, w[g][0].w, w[g][1].x, w[g][1].y, w[g][1].z, w[g][1].w};
+                split8(v, ws, ah[g], al[g]);
+            }
+            if (u + 1 < u1) load_w(u + 1);
             f32x16 main[PB], cross[PB];
             clear(main, cross);
-            const int s = windows(many, main, cross, [&](int sw, uint32_t lo, bool last) {
-                for (int c0 = 0; c0 < p.Cin; c0 += p.CK) {
-                    if (PARTS || WIN) {
-                        __syncthreads();
-                        stage(c0, pow2(sw), lo);
-                        __syncthreads();
-                    }
-                    int g0, g1;
-                    part(c0, g0, g1);
-                    const bool more = c0 + p.CK < p.Cin;
-                    const u32x4 *const nxt = stream(more || !last || u + 1 == uk ? u : u + 1, more ? c0 + p.CK : 0);
-                    contract<K, D, PB>(main, cross, a, stream(u, c0), nxt, g1 - g0, p.pitch, patch + 2 * g0 * p.TP, plane, p.TP, lane_pix, lane);
+            const int centre = p.P * p.pitch + p.P;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                if (g >= p.G) break;
+#pragma unroll
+                for (int pb = 0; pb < PB; ++pb) {
+                    const u32x4 bh = patch[lane_pix[pb] + centre + 2 * g * p.TP], bl = patch[lane_pix[pb] + centre + 2 * g * p.TP + plane];
+                    cross[pb] = mma(al[g], bh, cross[pb]);
+                    main[pb] = mma(ah[g], bh, main[pb]);
+                    cross[pb] = mma(ah[g], bl, cross[pb]);
                 }
-            });
-            // parts of the contraction: added up in the order of the parts, in the patch (nobody reads it any more: a
-            // launch that splits the contraction has one unit per wavefront)
-            if (p.kg > 1) {
-                f32x4 *const sums = reinterpret_cast<f32x4 *>(patch);
-                __syncthreads();
-                if (kw > 0) {
-#pragma unroll
-                    for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            f32x4 v;
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) v[i] = main[pb][4 * q + i] + cross[pb][4 * q + i];
-                            sums[((wv * PB + pb) * 4 + q) * 64 + lane] = v;
-                        }
-                }
-                __syncthreads();
-                if (kw > 0) continue;
-                for (int k = 1; k < p.kg; ++k)
-#pragma unroll
-                    for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const f32x4 v = sums[(((wv + k) * PB + pb) * 4 + q) * 64 + lane];
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) cross[pb][4 * q + i] += v[i];
-                        }
             }
-            if (mb < nbk) finish(main, cross, s, mb, p.Cout, p.coff, bias + (u * p.cwn + cw) * 32, nullptr, p.raw, K * K);
+            if (mb < nb1) finish(main, cross, mb, p.Cout1, p.coff1, bias + ((uk + u) * p.cwn + cw) * 32, rows + wv * 32, p.w1, 1);
         }
-        if constexpr (!PARTS) {
-            // 1x1 kernels straight from memory (at most 64 input layers): lane = output layer j, eight input layers per
-            // half; the loads of the next block are in flight while this one is multiplied and stored
-            f32x4 w[4][2];
-            auto load_w = [&](int u) {
-                const int m = min(u * stride + first_block, nb1 - 1) * 32 + j;
-                const float *const wr = p.w1 + (size_t)(m < p.Cout1 ? m : 0) * p.Cin + 8 * h;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float *const at = wr + 16 * (g < p.G ? g : 0);
-                    w[g][0] = *reinterpret_cast<const f32x4_a4 *>(at);
-                    w[g][1] = *reinterpret_cast<const f32x4_a4 *>(at + 4);
-                }
-            };
-            if (u1 > 0) load_w(0);
-            for (int u = 0; u < u1; ++u) {
-                const int mb = u * stride + first_block;
-                uint32_t top = 0;
-                int odd = 0;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float v[8] = {w[g][0].x, w[g][0].y, w[g][0].z, w[g][0].w, w[g][1].x, w[g][1].y, w[g][1].z, w[g][1].w};
-                    top = max(top, magnitude8(v));
-                    odd |= odd8(v);
-                }
-                top = max(top, (uint32_t)__shfl_xor((int)top, 32, 64));
-                odd |= __shfl_xor(odd, 32, 64);
-                const int ex = scale_exponent(top);
-                const float ws = pow2(ex);
-                if (h == 0) rows[wv * 32 + j] = odd ? kPlainRow : ex;
-                u32x4 ah[4], al[4];
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float v[8] = {w[g][0].x, w[g][0].y, w[g][0].z, w[g][0].w, w[g][1].x, w[g][1].y, w[g][1].z, w[g][1].w};
-                    split8(v, ws, ah[g], al[g]);
-                }
-                if (u + 1 < u1) load_w(u + 1);
-                f32x16 main[PB], cross[PB];
-                clear(main, cross);
-                const int centre = p.P * p.pitch + p.P;
-                const int s = windows(many, main, cross, [&](int sw, uint32_t lo, bool) {
-                    if (WIN) {
-                        __syncthreads();
-                        stage(0, pow2(sw), lo);
-                        __syncthreads();
-                    }
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        if (g >= p.G) break;
-#pragma unroll
-                        for (int pb = 0; pb < PB; ++pb) {
-                            const u32x4 bh = patch[lane_pix[pb] + centre + 2 * g * p.TP], bl = patch[lane_pix[pb] + centre + 2 * g * p.TP + plane];
-                            cross[pb] = mma(al[g], bh, cross[pb]);
-                            main[pb] = mma(ah[g], bh, main[pb]);
-                            cross[pb] = mma(ah[g], bl, cross[pb]);
-                        }
-                    }
-                });
-                if (mb < nb1) finish(main, cross, s, mb, p.Cout1, p.coff1, bias + ((uk + u) * p.cwn + cw) * 32, rows + wv * 32, p.w1, 1);
-            }
-        }
-    };
-    if (one_window) run(std::false_type{});
-    else run(std::true_type{});
+    }
 }
 
 }  // namespace split
@@ -602,7 +516,7 @@ long long stretch_pixels(int npx, int H, int W, int P)
     return npx + (rows - 1) * P + images * (long long)P * (W + P) + 2ll * ((long long)P * (W + P) + P);
 }
 
-constexpr size_t kExpandFixed = 8 * 32 * 4 + 18 * 4;
+constexpr size_t kExpandFixed = 8 * 32 * 4 + 16 * 4;
 
 struct ExpandPlan {
     ExpandParams p;
@@ -678,7 +592,7 @@ bool plan_expand(const ConvArgs &a, const ConvArgs *a1, const void *wk, ExpandPl
     p.TP = (int)TP; p.dTP = make_fastdiv(p.TP); p.tiles = (int)tiles;
     const size_t patch = std::max<size_t>((size_t)p.CK * per_layer, p.kg > 1 ? (size_t)pl.waves * 4096 * pl.PB : 0);
     p.patch_elems = (int)(patch / 16);
-    pl.lds = patch + kExpandFixed + ((size_t)(p.TP + 1) & ~(size_t)1) * 4 + units * p.cwn * 32 * 8;
+    pl.lds = patch + kExpandFixed + units * p.cwn * 32 * 8;
     return pl.lds <= (size_t)kLdsBytes;
 }
 

@@ -21,7 +21,6 @@
 #include "split_common.h"
 
 #include <algorithm>
-#include <type_traits>
 
 namespace sq {
 namespace stem {
@@ -43,7 +42,7 @@ template <bool SPLIT, bool POOL> struct Shape {
     static constexpr int ITEMS = PR * PAIRS, PER = (ITEMS + THREADS - 1) / THREADS;   // column pairs of all three layers per thread
     static constexpr int PLANE = 3 * PR * kRowDw;                     // dwords of one plane of the patch
     static constexpr int MAP = SPLIT ? 36 : 20;                       // dwords per pixel of a block of 32 layers on its way to the pooling
-    static constexpr size_t LDS = (size_t)3 * kSteps * NP * 1024 + (size_t)NP * PLANE * 4 + (POOL ? (size_t)(256 + 56) * MAP * 4 : 0) + 96 * 8 + 10 * 8 + 32 * 8 + (POOL ? (SPLIT ? 8 * 2 * 1024 : 6 * 1024) : 0);
+    static constexpr size_t LDS = (size_t)3 * kSteps * NP * 1024 + (size_t)NP * PLANE * 4 + (POOL ? (size_t)(256 + 56) * MAP * 4 : 0) + 96 * 8 + 10 * 8 + 32 * 8 + (POOL ? 6 * NP * 1024 + (SPLIT ? 8 * 2 * 1024 : 0) : 0);
 };
 
 struct Params {
@@ -76,16 +75,17 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
     uint32_t *const patch = reinterpret_cast<uint32_t *>(wl + 3 * kSteps * NP * 64);
     float *const map = reinterpret_cast<float *>(patch + NP * S::PLANE);                       // POOL: a block of 32 layers of the tile, and its pooled pixels
     float *const pooled = map + 256 * S::MAP;
-    int2 *const sb = reinterpret_cast<int2 *>(map + (POOL ? (256 + 56) * S::MAP : 0));            // [96] (exponent, bias)
-    uint2 *const red = reinterpret_cast<uint2 *>(sb + 96);                                     // [8 wavefronts] largest and smallest magnitude, [8] (an infinity or NaN in the kernels, in the squeeze kernels), -
+    int2 *const sb = reinterpret_cast<int2 *>(map + (POOL ? (256 + 56) * S::MAP : 0));            // [96] (scale's exponent, bias)
+    uint2 *const red = reinterpret_cast<uint2 *>(sb + 96);                                     // [8 wavefronts] range of the magnitudes, [8] (marks of the kernels' layers, whether squeeze kernels have marks), [9] (-, smallest magnitude of the kernels)
     int2 *const sbq = reinterpret_cast<int2 *>(red + 10);                                      // [32] of the squeeze
-    f32x4 *const parts = reinterpret_cast<f32x4 *>(sbq + 32);                                  // POOL: SPLIT: [8 wavefronts][2][64] its sums (16 layers); else its kernels [6][64]
+    u32x4 *const wq = reinterpret_cast<u32x4 *>(sbq + 32);                                     // POOL: its kernels [6][NP][64]
+    f32x4 *const parts = reinterpret_cast<f32x4 *>(wq + 6 * NP * 64);                          // POOL, SPLIT: [8 wavefronts][2][64] its sums (16 layers)
 
     const int t = threadIdx.x, lane = t & 63;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int j = lane & 31, h = lane >> 5;
     if (t < 96) sb[t] = int2{0, p.b && t < p.Cout ? __builtin_bit_cast(int, p.b[t]) : 0};
-    if (SPLIT && t == 0) red[8] = uint2{0, 0};
+    if (SPLIT && t == 0) { red[8] = uint2{0, 0}; red[9] = uint2{0, ~0u}; }
     if (POOL && t < 32) sbq[t] = int2{0, p.bsq && t < p.Csq ? __builtin_bit_cast(int, p.bsq[t]) : 0};
     // ---- kernels into LDS: [3 blocks][11 steps][NP][64 lanes][8]; lane l of step s = layer 32 * block + l % 32, kernel row
     // 2 s + l / 32 of the 21 (the 22nd is zero), eighth value zero
@@ -102,12 +102,17 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
             v[k][7] = 0.f;
         }
         __syncthreads();
+        uint32_t low = ~0u;                      // (of all layers together: marks no fewer than one by one would)
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
             const int e = t + k * S::THREADS;
-            if (e < kRows) atomicMax(reinterpret_cast<unsigned *>(&sb[e / 22].x), magnitude8(v[k]));
-            if (odd8(v[k])) red[8].x = 1;
+            Range range;
+            range.add8(v[k]);
+            low = min(low, range.low);
+            if (e < kRows) atomicMax(reinterpret_cast<unsigned *>(&sb[e / 22].x), range.top_bits());
         }
+        low = wave_min(low);
+        if (lane == 0) atomicMin(&red[9].y, low);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
@@ -120,7 +125,12 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
             wl[at + 64] = lo;
         }
         __syncthreads();
-        if (t < 96) sb[t].x = scale_exponent((uint32_t)sb[t].x);
+        if (t < 96) {
+            const uint32_t top = (uint32_t)sb[t].x;
+            const int word = row_word(scale_exponent(top), top, red[9].y);
+            if (word & (kOddRow | kWideRow)) atomicOr(&red[8].x, word & (kOddRow | kWideRow));
+            sb[t].x = row_exponent(word);
+        }
     } else {
         for (int e = t; e < 3 * kSteps * 64; e += S::THREADS) wl[e] = p.wp[e];
     }
@@ -152,29 +162,19 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
             }
         }
     };
-    constexpr uint32_t kWindow = 17u << 23;
-    // magnitudes of this thread's pixels (the largest of their three layers; an infinity or NaN: a smallest one of 0), to be
-    // joined over the workgroup
+    // range of the magnitudes of this thread's pixels, to be joined over the workgroup
     auto scan = [&]() {
-        uint32_t mx = 0, mn = 0xffffffffu;
+        Range range;
 #pragma unroll
         for (int k = 0; k < S::PER; ++k)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                uint32_t m = 0;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) m = max(m, __builtin_bit_cast(uint32_t, x[k][c][i]) & 0x7fffffffu);
-                const bool odd = m >= 0x7f800000u;
-                mx = max(mx, odd ? 0u : m);
-                if (m) mn = min(mn, odd ? 0u : m);
-            }
-        mx = wave_max(mx);
-        mn = wave_min(mn);
+            for (int c = 0; c < 3; ++c) range.add2(x[k][c][0], x[k][c][1]);
+        const uint32_t mx = wave_max(range.top_bits()), mn = wave_min(range.low);
         if (lane == 0) red[wv] = uint2{mx, mn};
     };
-    auto joined = [&](uint32_t &mx, uint32_t &mn) {
+    auto range = [&](uint32_t &mx, uint32_t &mn) {
         mx = 0;
-        mn = 0xffffffffu;
+        mn = ~0u;
         for (int k = 0; k < S::WAVES; ++k) {
             const uint2 r = red[k];
             mx = max(mx, r.x);
@@ -222,44 +222,61 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
             }
         }
     };
-    // (one accumulator: 33 additions where the fp32 instructions have 74)
     auto contract = [&](int cb, f32x16 &acc) {
         const u32x4 *const a = wl + cb * kSteps * NP * 64 + lane;
         u32x4 ah[2] = {a[0], a[0]}, al[2] = {a[(NP - 1) * 64], a[(NP - 1) * 64]};
+        f32x16 cross;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) cross[k] = 0.f;
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) {
             if constexpr (SPLIT) {
                 ah[(s + 1) & 1] = a[(s + 1 < kSteps ? s + 1 : s) * 128];
                 al[(s + 1) & 1] = a[(s + 1 < kSteps ? s + 1 : s) * 128 + 64];
                 __builtin_amdgcn_sched_barrier(0);
-                acc = mma(al[s & 1], b[s][0], acc);
-                acc = mma(ah[s & 1], b[s][NP - 1], acc);
+                cross = mma(al[s & 1], b[s][0], cross);
                 acc = mma(ah[s & 1], b[s][0], acc);
+                cross = mma(ah[s & 1], b[s][NP - 1], cross);
                 __builtin_amdgcn_sched_barrier(0);
             } else {
                 acc = mfma16<SPLIT>(a[s * 64], b[s][0], acc);
             }
         }
+        if constexpr (SPLIT) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) acc[k] = joined(acc[k], cross[k]);
+        }
     };
-    // A tile whose pixels' magnitudes span more than 2^17 or that holds an infinity or NaN (no photograph does): plain fp32
-    // sums from memory, brought to the scale es that the tile's sums have otherwise.
-    auto contract_wide = [&](int cb, int tile, int es, f32x16 &acc) {
+    // The contraction of a marked tile (no photograph is one), without its scale: where an infinity or NaN may be in it, and
+    // where a sum is too small for operands that are spread wide, on the fp32 instructions from memory (two of the 147
+    // products of a layer at a time).
+    auto contract_marked = [&](int cb, int tile, int es, bool odd, f32x16 &acc) {
         int n, r0, c0;
         corner(tile, n, r0, c0);
-        const int ih0 = 2 * (r0 + pr) - p.P, iw0 = 2 * (c0 + pc) - p.P;
-#pragma unroll 1
-        for (int tap = 0; tap < 147; ++tap) {
-            const int c = tap / 49, i = tap / 7 - 7 * c, jx = tap - 7 * (tap / 7), ih = ih0 + i, iw = iw0 + jx;
-            const bool ok = ih >= 0 && ih < p.H && iw >= 0 && iw < p.W;
-            const float v = buf_ld_in<TIN>(rin, ok ? (uint32_t)(((n * 3 + c) * p.H + ih) * p.W + iw) * ESZ : kOob, 0u);
+        bool again = odd;
+        if (!odd) {
+            contract(cb, acc);
+            const bool there = r0 + pr < p.Ho && c0 + pc < p.Wo;
+            float least = kSmall;
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
                 const int m = cb * 32 + 8 * (k >> 2) + 4 * h + (k & 3);
-                acc[k] = __builtin_fmaf(v, m < p.Cout ? p.w[m * 147 + tap] : 0.f, acc[k]);
+                least = fminf(least, there && m < p.Cout ? fabsf(acc[k]) : kSmall);
+                acc[k] = __builtin_amdgcn_ldexpf(acc[k], -es - sb[m].x);
             }
+            again = __ballot(least < kSmall) != 0;
         }
+        if (!again) return;
+        const int ih0 = 2 * (r0 + pr) - p.P, iw0 = 2 * (c0 + pc) - p.P, m = cb * 32 + j;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc[k] = __builtin_amdgcn_ldexpf(acc[k], es + sb[cb * 32 + 8 * (k >> 2) + 4 * h + (k & 3)].x);
+        for (int k = 0; k < 16; ++k) acc[k] = 0.f;
+#pragma unroll 2
+        for (int s = 0; s < 74; ++s) {
+            const int tap = 2 * s + h, c = tap / 49, i = tap / 7 - 7 * c, jx = tap - 7 * (tap / 7), ih = ih0 + i, iw = iw0 + jx;
+            const bool ok = tap < 147 && ih >= 0 && ih < p.H && iw >= 0 && iw < p.W;
+            const float v = buf_ld_in<TIN>(rin, ok ? (uint32_t)(((n * 3 + c) * p.H + ih) * p.W + iw) * ESZ : kOob, 0u);
+            acc = Mfma<32>::run(tap < 147 && m < p.Cout ? p.w[m * 147 + tap] : 0.f, v, acc);
+        }
     };
 
     // ---- POOL: the squeeze of a tile's 56 pooled pixels, two blocks of 32.  bfloat16: wavefronts 0 and 1 have a block each
@@ -267,37 +284,38 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
     // other block of 32 layers, and the sums of the four that share a block of pixels are added up at the end.
     const int qblk = SPLIT ? (wv >> 1) & 1 : wv & 1, qg = SPLIT ? wv & 1 : 0;
     const bool squeezer = POOL && (SPLIT || wv < 2);
-    u32x4 wq[2][NP];                                        // (bfloat16: in LDS)
     if (POOL && SPLIT) {
-        const bool ok = j < p.Csq;
-        const float *const row = p.wsq32 + (ok ? j : 0) * 96 + 8 * h;
-        auto eight = [&](int g, float (&v)[8]) {
-            const f32x4 lo = *reinterpret_cast<const f32x4_a4 *>(row + 16 * g), hi = *reinterpret_cast<const f32x4_a4 *>(row + 16 * g + 4);
+        if (wv < 6) {                                       // step wv of the six
+            const bool ok = j < p.Csq;
+            const float *const row = p.wsq32 + (ok ? j : 0) * 96 + 8 * h;
+            auto eight = [&](int g, float (&v)[8]) {
+                const f32x4 lo = *reinterpret_cast<const f32x4_a4 *>(row + 16 * g), hi = *reinterpret_cast<const f32x4_a4 *>(row + 16 * g + 4);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) { v[k] = ok ? lo[k] : 0.f; v[4 + k] = ok ? hi[k] : 0.f; }
-        };
-        uint32_t top = 0;
-        for (int g = 0; g < 6; ++g) {
+                for (int k = 0; k < 4; ++k) { v[k] = ok ? lo[k] : 0.f; v[4 + k] = ok ? hi[k] : 0.f; }
+            };
+            Range range;
             float v[8];
-            eight(g, v);
-            top = max(top, magnitude8(v));
-            if (odd8(v)) red[8].y = 1;
+            for (int g = 0; g < 6; ++g) {
+                eight(g, v);
+                range.add8(v);
+            }
+            const uint32_t top = max(range.top_bits(), (uint32_t)__shfl_xor((int)range.top_bits(), 32, 64));
+            const uint32_t low = min(range.low, (uint32_t)__shfl_xor((int)range.low, 32, 64));
+            if (top >= kOddMagnitude || spread(top, low)) red[8].y = 1;
+            const int e = scale_exponent(top);
+            eight(wv, v);
+            u32x4 hi, lo;
+            split8(v, pow2(e), hi, lo);
+            wq[(wv * 2) * 64 + lane] = hi;
+            wq[(wv * 2 + 1) * 64 + lane] = lo;
+            if (h == 0 && wv == 0) sbq[j].x = e;
         }
-        top = max(top, (uint32_t)__shfl_xor((int)top, 32, 64));
-        const int e = scale_exponent(top);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {                       // wavefronts 0..3: blocks 0 and 2 of the layers; 4..7: block 1
-            float v[8];
-            eight((wv < 4 ? 4 * k : 2) + qg, v);
-            split8(v, pow2(e), wq[k][0], wq[k][NP - 1]);
-        }
-        if (h == 0 && wv == 0) sbq[j].x = e;
     } else if (POOL) {
-        if (t < 6 * 64) reinterpret_cast<u32x4 *>(parts)[t] = p.wsq[t];
+        if (t < 6 * 64) wq[t] = p.wsq[t];
     }
     const int pp = 32 * qblk + j, ppc = POOL ? min(pp, 55) : 0;
-    f32x16 sum;                      // of the squeeze
-    float plain[8];                  // SPLIT: and, without its scale, what steps with an infinity or NaN add to it
+    f32x16 sum, sum_cross;           // of the squeeze; SPLIT: its cross terms
+    bool plain = false;              // SPLIT: whether `parts` holds, without the scale, what steps added that no scale holds
     int sq_e = 127;                  // SPLIT: exponent of this pixel's scale, and the magnitude up to which it serves
     uint32_t sq_limit = 0;
     // 56 pooled pixels x 8 groups of four layers of a block, one per thread
@@ -331,68 +349,84 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
                 uint2{(__builtin_bit_cast(uint32_t, v[0]) >> 16) | (__builtin_bit_cast(uint32_t, v[1]) & 0xffff0000u),
                       (__builtin_bit_cast(uint32_t, v[2]) >> 16) | (__builtin_bit_cast(uint32_t, v[3]) & 0xffff0000u)};
     };
-    auto squeeze_block = [&](auto block, int es) {
-        constexpr int cb = decltype(block)::value;
+    auto squeeze_block = [&](int cb, int es, bool scaled) {
         if (SPLIT && (cb == 1) != (wv >= 4)) return;
 #pragma unroll
         for (int k0 = 0; k0 < (SPLIT ? 1 : 2); ++k0) {
             const int g = SPLIT ? qg : k0;
             if constexpr (SPLIT) {
-                constexpr int kq = cb == 2 ? 1 : 0;
                 const f32x4 *const at = reinterpret_cast<const f32x4 *>(pooled + ppc * S::MAP + 16 * g + 8 * h);
                 const f32x4 lo = at[0], hi = at[1];
+                const u32x4 ah = wq[(2 * cb + g) * 128 + lane], al = wq[(2 * cb + g) * 128 + 64 + lane];
                 float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     const int2 f = sb[cb * 32 + 16 * g + 8 * h + k];
-                    v[k] = fmaxf(__builtin_amdgcn_ldexpf(v[k], -es - f.x) + __builtin_bit_cast(float, f.y), 0.f);
+                    v[k] = fmaxf(__builtin_amdgcn_ldexpf(v[k], scaled ? -es - f.x : 0) + __builtin_bit_cast(float, f.y), 0.f);
                 }
-                if (__ballot(odd8(v)) || red[8].y) {           // in fp32 then
+                Range range;
+                range.add8(v);
+                uint32_t mag = range.top_bits();
+                const auto tops = __builtin_amdgcn_permlane32_swap(mag, mag, false, false), lows = __builtin_amdgcn_permlane32_swap(range.low, range.low, false, false);
+                mag = max((uint32_t)tops[0], (uint32_t)tops[1]);
+                const uint32_t low = min((uint32_t)lows[0], (uint32_t)lows[1]);
+                // The scale follows the largest magnitude met.  A step that would bring the sums before it down by 2^64 or
+                // more, that holds a value below 2^-25 of that magnitude, an infinity or NaN, and every step where the
+                // kernels hold such values, is added up in fp32.
+                const bool up = mag > sq_limit;
+                const int en = up ? scale_exponent(mag) : sq_e;
+                const uint32_t made_for = up ? mag : max(sq_limit, 1u << 23) - (1u << 23);
+                if (__ballot(mag >= kOddMagnitude || spread(made_for, low) || (sq_limit && sq_e - en >= 64)) || red[8].y) {
+                    // (rare: kept small, its sums in LDS, so that the ordinary steps keep their registers)
+                    float *const own = reinterpret_cast<float *>(parts + wv * 128 + lane);
 #pragma unroll 1
-                    for (int k = 0; k < 16; ++k) {
-                        const int c = 16 * g + k;
-                        const int2 f = sb[cb * 32 + c];
-                        const float u = fmaxf(__builtin_amdgcn_ldexpf(pooled[ppc * S::MAP + c], -es - f.x) + __builtin_bit_cast(float, f.y), 0.f);
-#pragma unroll
-                        for (int r = 0; r < 8; ++r) {
-                            const int m = 8 * (r >> 2) + 4 * h + (r & 3);
-                            plain[r] = __builtin_fmaf(u, m < p.Csq ? p.wsq32[m * 96 + cb * 32 + c] : 0.f, plain[r]);
+                    for (int r = 0; r < 8; ++r) {
+                        const int m = 8 * (r >> 2) + 4 * h + (r & 3);
+                        float *const to = own + (r >> 2) * 256 + (r & 3);
+                        const float *const w = p.wsq32 + (m < p.Csq ? m : 0) * 96 + cb * 32 + 16 * g;
+                        float add = plain ? *to : 0.f;
+#pragma unroll 1
+                        for (int k = 0; k < 16; ++k) {
+                            const int2 f = sb[cb * 32 + 16 * g + k];
+                            const float u = fmaxf(__builtin_amdgcn_ldexpf(pooled[ppc * S::MAP + 16 * g + k], scaled ? -es - f.x : 0) + __builtin_bit_cast(float, f.y), 0.f);
+                            add = __builtin_fmaf(u, w[k], add);
                         }
+                        *to = add;
                     }
+                    plain = true;
                     return;
                 }
-                uint32_t mag = magnitude8(v);
-                const auto both = __builtin_amdgcn_permlane32_swap(mag, mag, false, false);
-                mag = max((uint32_t)both[0], (uint32_t)both[1]);
-                const bool up = mag > sq_limit;
                 if (__ballot(up)) {
-                    const int en = up ? scale_exponent(mag) : sq_e;
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) sum[k] = __builtin_amdgcn_ldexpf(sum[k], en - sq_e);
+                    for (int k = 0; k < 8; ++k) {             // (at most 16 layers: the other registers hold none)
+                        sum[k] = __builtin_amdgcn_ldexpf(sum[k], en - sq_e);
+                        sum_cross[k] = __builtin_amdgcn_ldexpf(sum_cross[k], en - sq_e);
+                    }
                     sq_e = en;
                     if (up) sq_limit = mag + (1u << 23);      // twice the magnitude the scale was made for: below 2^15
                 }
                 u32x4 bh, bl;
                 split8(v, pow2(sq_e), bh, bl);
-                sum = mma(wq[kq][NP - 1], bh, sum);
-                sum = mma(wq[kq][0], bl, sum);
-                sum = mma(wq[kq][0], bh, sum);
+                sum_cross = mma(al, bh, sum_cross);
+                sum = mma(ah, bh, sum);
+                sum_cross = mma(ah, bl, sum_cross);
             } else {
                 const u32x4 o = *reinterpret_cast<const u32x4 *>(pooled + ppc * S::MAP + 8 * g + 4 * h);
-                sum = mfma16<SPLIT>(reinterpret_cast<const u32x4 *>(parts)[(2 * cb + k0) * 64 + lane], o, sum);
+                sum = mfma16<SPLIT>(wq[(2 * cb + k0) * 64 + lane], o, sum);
             }
         }
     };
 
     const XcdShare share = xcd_share((int)blockIdx.x, (int)gridDim.x, p.tiles);
     int tile = share.first, es = 0;
-    bool wide = false;
+    bool odd = false, marked = false;
     // scale of the patch in the registers (after scan() and a barrier), and the patch
     auto settle = [&]() {
         if constexpr (SPLIT) {
             uint32_t mx, mn;
-            joined(mx, mn);
-            wide = mn == 0 || red[8].x || (mx != 0 && mx - mn >= kWindow);
+            range(mx, mn);
+            odd = mx >= kOddMagnitude || (__builtin_amdgcn_readfirstlane(red[8].x) & kOddRow);
+            marked = odd || spread(mx, mn) || __builtin_amdgcn_readfirstlane(red[8].x);
             es = scale_exponent(mx);
         }
         stash(es);
@@ -428,16 +462,18 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
         const bool more = tile + share.step < share.end;
         __syncthreads();               // the patch is complete
         const int es_now = es;
-        const bool wide_now = wide;
+        const bool odd_now = odd, marked_now = SPLIT && marked;
         operands();
         if (more) fetch(tile + share.step);
         if constexpr (POOL) {
             if (SPLIT) emit();            // of the tile before
             if (squeezer) {
 #pragma unroll
-                for (int k = 0; k < 16; ++k) sum[k] = SPLIT ? 0.f : __builtin_bit_cast(float, sbq[8 * (k >> 2) + 4 * h + (k & 3)].y);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) plain[k] = 0.f;
+                for (int k = 0; k < 16; ++k) {
+                    sum[k] = SPLIT ? 0.f : __builtin_bit_cast(float, sbq[8 * (k >> 2) + 4 * h + (k & 3)].y);
+                    sum_cross[k] = 0.f;
+                }
+                plain = false;
                 sq_e = 127;
                 sq_limit = 0;
             }
@@ -448,7 +484,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
 #pragma unroll
             for (int k = 0; k < 16; ++k)      // (bfloat16: bias first, as in the other kernels on such maps)
                 acc[k] = SPLIT ? 0.f : __builtin_bit_cast(float, sb[cb * 32 + 8 * (k >> 2) + 4 * h + (k & 3)].y);
-            if (SPLIT && wide_now) contract_wide(cb, tile, es_now, acc);
+            if (marked_now) contract_marked(cb, tile, es_now, odd_now, acc);
             else contract(cb, acc);
             if constexpr (POOL) {
                 {
@@ -470,11 +506,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
                 pool_block();
                 if (more && cb == 0) settle();
                 __syncthreads();
-                if (squeezer) {
-                    if (cb == 0) squeeze_block(std::integral_constant<int, 0>{}, es_now);
-                    else if (cb == 1) squeeze_block(std::integral_constant<int, 1>{}, es_now);
-                    else squeeze_block(std::integral_constant<int, 2>{}, es_now);
-                }
+                if (squeezer) squeeze_block(cb, es_now, !marked_now);
             } else {
                 int n, r0, c0;
                 corner(tile, n, r0, c0);
@@ -487,7 +519,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
                     for (int i = 0; i < 4; ++i) {
                         const int m = cb * 32 + 8 * q + 4 * h + i;
                         const int2 f = sb[m];
-                        const float v = SPLIT ? __builtin_amdgcn_ldexpf(acc[4 * q + i], -es_now - f.x) + __builtin_bit_cast(float, f.y) : acc[4 * q + i];
+                        const float v = SPLIT ? __builtin_amdgcn_ldexpf(acc[4 * q + i], marked_now ? 0 : -es_now - f.x) + __builtin_bit_cast(float, f.y) : acc[4 * q + i];
                         buf_st(rout, m < p.Cout ? o : kOob, (uint32_t)(cb * 32 + 8 * q + i) * plane4, fmaxf(v, lowest));
                     }
                 if (more && cb == 2) {
@@ -504,7 +536,12 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
                     if (8 * q < p.Csq) {
                         f32x4 v;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_ldexpf(sum[4 * q + i], -sq_e - sbq[8 * q + 4 * h + i].x) + plain[4 * q + i];
+                        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_ldexpf(joined(sum[4 * q + i], sum_cross[4 * q + i]), -sq_e - sbq[8 * q + 4 * h + i].x);
+                        if (plain) {
+                            const f32x4 add = parts[(wv * 2 + q) * 64 + lane];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) v[i] += add[i];
+                        }
                         parts[(wv * 2 + q) * 64 + lane] = v;
                     }
                 last_tile = tile;

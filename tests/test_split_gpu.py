@@ -252,3 +252,100 @@ def test_one_launch_first_layers_with_infinities_and_nan(sq, where):
     want = network_of_single_layers(sq, xd[pick].contiguous(), pd).cpu().numpy()
     assert np.isfinite(want).all()
     assert_close(got[pick].cpu().numpy(), want, where)
+
+
+# Values far apart that never meet: a sum is as exact as its own terms, whatever lies beside them under zero kernels or meets
+# zeros.  2^20, 2^27 and more apart: within a scale's reach, at its end, and far outside it.
+APART = [1e6, 2e8, 1e12, 1e30]
+
+
+@pytest.mark.parametrize("big", APART)
+@pytest.mark.parametrize("cin,cout,k,h,w_", [(16, 64, 3, 9, 11), (64, 32, 3, 27, 27), (384, 64, 3, 11, 13), (96, 40, 5, 30, 20), (3, 96, 7, 50, 61)])
+@pytest.mark.parametrize("where", ["layer under zero kernels", "kernels over a zero layer", "single kernels over a zero layer", "one kernel"])
+def test_sums_are_as_exact_as_their_own_terms(sq, cin, cout, k, h, w_, big, where):
+    rng = np.random.default_rng(cin + k)
+    stride, pad = (2, 2) if k == 7 else (1, (k - 1) // 2)
+    x = np.maximum(synth.normal01(rng, (2, cin, h, w_)), 0)
+    w, b = synth.conv_params(rng, cout, cin, k)
+    if where == "layer under zero kernels":
+        x[:, 1] = big
+        w[:, 1] = 0
+    elif where == "kernels over a zero layer":
+        x[:, 1] = 0
+        w[:, 1] *= np.float32(big)
+    elif where == "single kernels over a zero layer":
+        x[:, 2] = 0
+        w[7, 2, 1, 1] = big
+    else:                      # a pruned layer: one kernel of ordinary size, over small values beside large ones
+        x[:, 0] *= np.float32(1 / big)
+        w[3] = 0
+        w[3, 0, k // 2, k // 2] = 0.75
+        b[3] = 0
+    b *= np.float32(1e-3)
+    got = (sq.sq_conv2d_forward if k == 7 else sq.sq_conv2d_forward_ws)(dev(x), dev(w), dev(b), stride, pad, True).cpu().numpy()
+    assert_within_rounding(got, oracle.conv2d(x, w, b, stride, pad, True), x, w, b, pad, (where, big), stride)
+
+
+@pytest.mark.parametrize("big", APART)
+@pytest.mark.parametrize("n,csq,ce", [(3, 48, 64), (24, 64, 256)])
+def test_fire_sums_are_as_exact_as_their_own_terms(sq, n, csq, ce, big):
+    rng = np.random.default_rng(csq)
+    x = synth.uniform01(rng, (n, 32, 27, 27))
+    p = [*synth.conv_params(rng, csq, 32, 1), *synth.conv_params(rng, ce, csq, 1), *synth.conv_params(rng, ce, csq, 3)]
+    p[0][5] = np.abs(p[0][5]) * np.float32(big)                            # a squeeze layer that no expand kernel reads
+    p[2][:, 5] = p[4][:, 5] = 0
+    p[0][6], p[1][6] = -np.abs(p[0][6]), 0                                 # one that is zero after the ReLU, under large kernels
+    p[2][3, 6] = p[4][9, 6] = big
+    d = [dev(a) for a in [x] + p]
+    got = sq.sq_fire_forward(*d)
+    assert torch.equal(sq.sq_fire_forward_packed(*d, sq.sq_fire_pack_weights(d[5])), got)
+    s = sq.sq_conv2d_forward(d[0], d[1], d[2], 1, 0, True).cpu().numpy()
+    assert s[:, 5].min() > 0 and s[:, 6].max() == 0
+    g = got.cpu().numpy()
+    assert_within_rounding(g[:, :ce], oracle.conv2d(s, p[2], p[3], 1, 0, True), s, p[2], p[3], 0, "expand1x1")
+    assert_within_rounding(g[:, ce:], oracle.conv2d(s, p[4], p[5], 1, 1, True), s, p[4], p[5], 1, "expand3x3")
+
+
+@pytest.mark.parametrize("big", APART)
+@pytest.mark.parametrize("first", [True, False])                           # the large layer before and after those that count
+def test_classifier_sums_are_as_exact_as_their_own_terms(sq, big, first):
+    n, cin, cout, h, w = 40, 256, 500, 13, 13
+    rng = np.random.default_rng(9)
+    x = synth.uniform01(rng, (n, cin, h, w))
+    wt, b = synth.conv_params(rng, cout, cin, 1)
+    at, zero = (3, 250) if first else (250, 3)
+    x[:20, at], wt[:, at] = big, 0
+    x[20:, zero], wt[7, zero] = 0, big
+    x[:20, zero] = 0
+    x[20:, at] = 0
+    sq.sq_profile_begin(16)
+    _, means = sq.sq_classifier_forward(dev(x), dev(wt), dev(b), want_means=True)
+    assert any("k1s1_split_96+planesums" in r["name"] for r in sq.sq_profile_end())
+    ref = oracle.conv2d(x, wt, b, 1, 0, True).astype(np.float64).mean(axis=(2, 3))
+    terms = oracle.conv2d(np.abs(x), np.abs(wt), np.abs(b), 1, 0, False).astype(np.float64).mean(axis=(2, 3))
+    err = np.abs(means.cpu().numpy() - ref)
+    assert (err <= (3 * cin / 16 + h * w + 16) * 2.0 ** -24 * terms).all(), float((err / terms).max())
+
+
+@pytest.mark.parametrize("big", APART)
+@pytest.mark.parametrize("where", ["layer under zero kernels", "kernels over a zero layer", "image layer under zero kernels"])
+def test_one_launch_first_layers_are_as_exact_as_their_own_terms(sq, big, where):
+    """Layers that count for nothing, large and absent: the same probabilities but for rounding."""
+    cfg = synth.config_squeezenet(seed=78, n=10)
+    x, params = cfg["x"].copy(), [p.copy() for p in cfg["params"]]
+    for c in (2, 40):                                    # the first and the second step that a wavefront adds
+        if where == "layer under zero kernels":
+            params[0][c], params[2][:, c] = np.abs(params[0][c]) * np.float32(big), 0
+        elif where == "kernels over a zero layer":
+            params[0][c], params[1][c], params[2][3, c] = -np.abs(params[0][c]), 0, big
+        else:
+            x[:, 1], params[0][:, 1] = big, 0
+    run = lambda x, params: sq.sq_squeezenet_forward_packed(dev(x), params, sq.sq_pack_weights(params, sq.SQ_F32)).cpu().numpy().astype(np.float64)
+    got = run(x, [dev(p) for p in params])
+    for c in (2, 40):
+        if where == "image layer under zero kernels":
+            x[:, 1] = 0
+        else:
+            params[0][c], params[2][:, c] = 0, 0
+    want = run(x, [dev(p) for p in params])
+    assert np.abs(got / want - 1).max() <= 1e-5, float(np.abs(got / want - 1).max())
