@@ -136,7 +136,6 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
     }
 
     const rsrc_t rin = make_rsrc(p.in, p.in_bytes), rout = make_rsrc(p.out, p.out_bytes);
-    const float lowest = POOL || p.relu ? 0.f : -__builtin_inff();
     auto corner = [&](int tile, int &n, int &r0, int &c0) {
         n = fdiv(tile, p.dPer);
         const int rem = tile - n * p.per_image, rg = fdiv(rem, p.dCG);
@@ -520,7 +519,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
                         const int m = cb * 32 + 8 * q + 4 * h + i;
                         const int2 f = sb[m];
                         const float v = SPLIT ? __builtin_amdgcn_ldexpf(acc[4 * q + i], marked_now ? 0 : -es_now - f.x) + __builtin_bit_cast(float, f.y) : acc[4 * q + i];
-                        buf_st(rout, m < p.Cout ? o : kOob, (uint32_t)(cb * 32 + 8 * q + i) * plane4, fmaxf(v, lowest));
+                        buf_st(rout, m < p.Cout ? o : kOob, (uint32_t)(cb * 32 + 8 * q + i) * plane4, p.relu ? fmaxf(v, 0.f) : v);      // (without ReLU a NaN stays one)
                     }
                 if (more && cb == 2) {
                     if (SPLIT) scan();

@@ -349,3 +349,15 @@ def test_one_launch_first_layers_are_as_exact_as_their_own_terms(sq, big, where)
             params[0][c], params[2][:, c] = 0, 0
     want = run(x, [dev(p) for p in params])
     assert np.abs(got / want - 1).max() <= 1e-5, float(np.abs(got / want - 1).max())
+
+
+def test_first_layer_without_relu_keeps_nan(sq):
+    rng = np.random.default_rng(6)
+    x = synth.uniform01(rng, (2, 3, 40, 33))
+    x[0, 1, 20, 9], x[1, 2, 3, 30] = np.nan, np.inf
+    w, b = synth.conv_params(rng, 96, 3, 7)
+    want = sq.sq_conv2d_forward_ex(dev(x), dev(w), dev(b), 2, 2, False, algo=sq.SQ_ALGO_DIRECT).cpu().numpy()
+    got = sq.sq_conv2d_forward(dev(x), dev(w), dev(b), 2, 2, False).cpu().numpy()
+    assert np.isnan(want).any() and np.isinf(want).any()
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    np.testing.assert_array_equal(got[np.isinf(want)], want[np.isinf(want)])
