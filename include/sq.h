@@ -315,13 +315,13 @@ int sq_fire_forward_static(const void *in, const void *w_sq, const float *b_sq,
 /*
  * The fire layer on kernels re-ordered ahead of time (section "Zero-overhead Vectorization":
  * the paper re-orders the kernels once, offline, into the order its threads read them).
- * Here the re-ordered form of the expand3x3 kernels is what the matrix-core lanes load: for Csq
- * 48 or 64 every value as two f16 values (scaled per output layer), else the
- * minimal-filtering transform G g G^T.
+ * Here the re-ordered form of the expand3x3 kernels is what the matrix-core lanes load: the
+ * minimal-filtering transform G g G^T, and for Csq 48 or 64 also every value as two f16 values
+ * (scaled per output layer); which of them a call reads depends on its batch and map.
  *   sq_fire_packed_bytes(Csq, Ce3): size of that form; 0 = the shape has none (Csq not a
  *     multiple of 8 or Ce3 not a multiple of 32): use sq_fire_forward.
  *   sq_fire_pack_weights(): writes it from w_e3 [Ce3][Csq][3][3] (fp32) into `packed` (device,
- *     256-byte aligned, at least sq_fire_packed_bytes bytes).  One launch on the thread's stream.
+ *     256-byte aligned, at least sq_fire_packed_bytes bytes).  Launches on the thread's stream.
  *   sq_fire_forward_packed(): sq_fire_forward without the per-call transform; `packed_e3` is
  *     only read.  workspace: at least N*Csq*H*W*4 bytes rounded up to 256 (the squeeze map).
  * Errors: as sq_fire_forward; SQ_ERR_UNSUPPORTED where sq_fire_packed_bytes is 0.

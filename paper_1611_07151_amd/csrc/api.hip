@@ -610,15 +610,15 @@ int fire_checked(const void *in, const void *w_sq, const float *b_sq, const void
     const size_t need = packed_e3 ? map_bytes : sq_fire_workspace_bytes(N, H, W, Csq, Ce3);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need) return SQ_ERR_WORKSPACE;
     if (packed_e3 && ((uintptr_t)packed_e3 & 255)) return SQ_ERR_WORKSPACE;
-    if (packed_e3 && expand_split_shape(Csq, Ce3))   // (the other forms take these layers' kernels as they lie)
-        return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace, nullptr, 0, false,
-                         kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr, nullptr, true, packed_e3);
-    if (packed_e3)
-        return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace,
-                         const_cast<void *>(packed_e3), conv_workspace_bytes(Csq, Ce3, 3, 1, 1), true, kFireAlone);
+    const bool split = expand_split_shape(Csq, Ce3);
+    if (packed_e3) {
+        const size_t transforms = conv_workspace_bytes(Csq, Ce3, 3, 1, 1);
+        return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace, const_cast<void *>(packed_e3),
+                         transforms, true, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr, nullptr, split, split ? (const char *)packed_e3 + transforms : nullptr);
+    }
     return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace,
                      (char *)workspace + map_bytes, workspace_bytes - map_bytes, false, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr,
-                     nullptr, expand_split_shape(Csq, Ce3));
+                     nullptr, split);
 }
 }  // namespace
 
@@ -685,19 +685,22 @@ int sq_fire_forward_static(const void *in, const void *w_sq, const float *b_sq, 
 size_t sq_fire_packed_bytes(int Csq, int Ce3)
 {
     if (Csq <= 0 || Ce3 <= 0) return 0;
-    return conv_workspace_bytes(Csq, Ce3, 3, 1, 1);
+    // the transforms, and behind them, for shapes that run on split operands, the split kernels: which of the two a call reads
+    // depends on its batch and on the width of its map
+    return conv_workspace_bytes(Csq, Ce3, 3, 1, 1) + (expand_split_shape(Csq, Ce3) ? align_up(split_kernel_bytes(Ce3, Csq, 3), 256) : 0);
 }
 
 int sq_fire_pack_weights(const void *w_e3, void *packed, size_t packed_bytes, int Csq, int Ce3)
 {
     if (!w_e3 || !packed) return SQ_ERR_NULL;
     if (Csq <= 0 || Ce3 <= 0) return SQ_ERR_SHAPE;
-    const size_t need = conv_workspace_bytes(Csq, Ce3, 3, 1, 1);
-    if (!need) return SQ_ERR_UNSUPPORTED;   // this shape has no packed form: call sq_fire_forward
-    if (((uintptr_t)packed & 255) || packed_bytes < need) return SQ_ERR_WORKSPACE;
+    const size_t transforms = conv_workspace_bytes(Csq, Ce3, 3, 1, 1);
+    if (!transforms) return SQ_ERR_UNSUPPORTED;   // this shape has no packed form: call sq_fire_forward
+    if (((uintptr_t)packed & 255) || packed_bytes < sq_fire_packed_bytes(Csq, Ce3)) return SQ_ERR_WORKSPACE;
     const KernelPrepJob job{w_e3, packed, Csq, Ce3};
     set_stage("kernel transform");
-    const int rc = expand_split_shape(Csq, Ce3) ? split_kernels((const float *)w_e3, packed, Ce3, Csq, 3) : conv_prepare_kernels(&job, 1, SQ_F32);
+    int rc = conv_prepare_kernels(&job, 1, SQ_F32);
+    if (rc == SQ_OK && expand_split_shape(Csq, Ce3)) rc = split_kernels((const float *)w_e3, (char *)packed + transforms, Ce3, Csq, 3);
     set_stage("");
     return rc;
 }

@@ -361,3 +361,20 @@ def test_first_layer_without_relu_keeps_nan(sq):
     assert np.isnan(want).any() and np.isinf(want).any()
     np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
     np.testing.assert_array_equal(got[np.isinf(want)], want[np.isinf(want)])
+
+
+@pytest.mark.parametrize("csq,ce,w_", [(48, 64, 180), (48, 192, 260), (64, 64, 256), (64, 256, 176), (64, 32, 190)])
+@pytest.mark.parametrize("n", [1, 3, 6])
+def test_packed_fire_runs_the_kernels_of_the_unpacked_call_on_maps_of_any_width(sq, n, csq, ce, w_):
+    """Rows too long for the split form's patch in LDS (and around that line): the packed call has the kernels of every form."""
+    rng = np.random.default_rng(w_)
+    x = synth.uniform01(rng, (n, 16, 5, w_))
+    d = [dev(a) for a in [x, *synth.conv_params(rng, csq, 16, 1), *synth.conv_params(rng, ce, csq, 1), *synth.conv_params(rng, ce, csq, 3)]]
+    packed = sq.sq_fire_pack_weights(d[5])
+    results, names = [], []
+    for call, more in ((sq.sq_fire_forward, ()), (sq.sq_fire_forward_packed, (packed,))):
+        sq.sq_profile_begin(8)
+        results.append(call(*d, *more))
+        names.append([r["name"] for r in sq.sq_profile_end() if "transform" not in r["name"] and "split_kernels" not in r["name"]])
+    assert names[0] == names[1]
+    assert torch.equal(*results)
