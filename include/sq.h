@@ -371,15 +371,16 @@ size_t sq_squeezenet_workspace_bytes(int N);
  *   sq_packed_weights_bytes(dtype): size of the packed kernels for that mode.
  *   sq_pack_weights(params, dtype, packed, packed_bytes): writes them (device memory, 256-byte
  *     aligned) from the parameter table of sq_squeezenet_forward.  SQ_F32: the minimal-filtering
- *     transforms of the eight expand3x3 kernels (every other fp32 kernel is read as it lies);
+ *     transforms and the split form of the eight expand3x3 kernels (other fp32 kernels are read as they lie);
  *     SQ_BF16: all 26 kernels as bfloat16 in matrix-core operand order (the same bytes as
  *     sq_squeezenet_bf16_pack_params).  Not part of a timed forward pass.
  *   sq_squeezenet_forward_packed(): sq_squeezenet_forward without the per-call kernel
  *     transform (SQ_F32), or sq_squeezenet_forward_bf16 on an fp32 image (SQ_BF16); `packed`
  *     must have been written for the mode in force and is only read.  Workspace and taps as
- *     for sq_squeezenet_forward.  SQ_F32: the same result as sq_squeezenet_forward up to rounding
- *     (from ten images on, without taps, layers run on the f16 matrix instructions with each fp32
- *     operand split into two f16 values; otherwise bit for bit).
+ *     for sq_squeezenet_forward.  SQ_F32: the same result as sq_squeezenet_forward, bit for bit
+ *     below ten images and up to rounding from ten on, where layers run on the f16 matrix
+ *     instructions with each fp32 operand split into two f16 values (from 16 images on conv10 too,
+ *     whose kernels are split inside the call).
  * Errors: SQ_ERR_NULL, SQ_ERR_SHAPE, SQ_ERR_WORKSPACE (packed misaligned or too small),
  * SQ_ERR_UNSUPPORTED (unknown dtype, batch too large), SQ_ERR_HIP.
  */

@@ -173,7 +173,7 @@ ConvArgs make_args(const void *in, const void *w, const float *b, float *out, in
     a.out_channels = out_channels;
     a.c_offset = c_offset;
     a.dtype = dtype;
-    a.ws = nullptr; a.ws_bytes = 0; a.ws_ready = false;
+    a.ws = nullptr; a.ws_bytes = 0; a.ws_ready = 0;
     a.pool_H = a.pool_W = 0;
     return a;
 }
@@ -188,7 +188,7 @@ ConvArgs make_args(const void *in, const void *w, const float *b, float *out, in
 int fire_impl(const void *in, const void *w_sq, const float *b_sq, const void *w_e1,
               const float *b_e1, const void *w_e3, const float *b_e3, float *out, int N, int Cin,
               int H, int W, int Csq, int Ce1, int Ce3, float *sq_map, void *conv_ws, size_t conv_ws_bytes,
-              bool conv_ws_ready, const char *const *stages, int pool_H = 0, int pool_W = 0, int sq_algo = SQ_ALGO_AUTO,
+              int conv_ws_ready, const char *const *stages, int pool_H = 0, int pool_W = 0, int sq_algo = SQ_ALGO_AUTO,
               const ColPool *cp_in = nullptr, const ColPool *cp_out = nullptr, bool split = false, const void *split_e3 = nullptr, bool have_sq = false)
 {
     ConvArgs a1 = make_args(sq_map, w_e1, b_e1, out, N, Csq, H, W, Ce1, 1, 1, 0, 1, Ce1 + Ce3, 0, SQ_F32);
@@ -488,7 +488,7 @@ int sq_tune_fire_forward_poolcols(const float *in, const float *w_sq, const floa
     cp.row_stride = colpool_row_stride(W, 4);
     geometry[0] = cp.shift; geometry[1] = cp.slots_row; geometry[2] = cp.slots_image; geometry[3] = cp.row_stride;
     return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace,
-                     (char *)workspace + map_bytes, workspace_bytes - map_bytes, false, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr, &cp);
+                     (char *)workspace + map_bytes, workspace_bytes - map_bytes, 0, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr, &cp);
 }
 
 int sq_tune_poolrows_conv2d_forward(const float *in, const float *w, const float *b, float *out, int N, int Cin, int H, int W,
@@ -614,10 +614,10 @@ int fire_checked(const void *in, const void *w_sq, const float *b_sq, const void
     if (packed_e3) {
         const size_t transforms = conv_workspace_bytes(Csq, Ce3, 3, 1, 1);
         return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace, const_cast<void *>(packed_e3),
-                         transforms, true, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr, nullptr, split, split ? (const char *)packed_e3 + transforms : nullptr);
+                         transforms, kReadyBoth, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr, nullptr, split, split ? (const char *)packed_e3 + transforms : nullptr);
     }
     return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace,
-                     (char *)workspace + map_bytes, workspace_bytes - map_bytes, false, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr,
+                     (char *)workspace + map_bytes, workspace_bytes - map_bytes, 0, kFireAlone, 0, 0, SQ_ALGO_AUTO, nullptr,
                      nullptr, split);
 }
 }  // namespace
@@ -747,6 +747,21 @@ size_t packed_f32_bytes()
     for (const FireCfg &fc : kFires) b += conv_workspace_bytes(fc.sq, fc.e, 3, 1, 1);
     return b;
 }
+
+// Where the packed fp32 kernels of a layer lie.  Transforms have two layouts, of which each fire layer of the network runs
+// one (fire2, 3, 5, 9 the first, fire4, 6, 7, 8 the second): both are written side by side, and the split kernels then
+// take the place of the other one (36 bytes per weight in 64).
+struct PackedLayer {
+    size_t transforms, split;      // `transforms` as the area of both layouts, of which `ready` is there
+    int ready;
+};
+PackedLayer packed_layer(int f)
+{
+    PackedLayer p = {0, 0, f == 2 || (f >= 4 && f <= 6) ? kReadyAuto : kReadyShared};
+    for (int g = 0; g < f; ++g) p.transforms += conv_workspace_bytes(kFires[g].sq, kFires[g].e, 3, 1, 1);
+    p.split = p.transforms + (p.ready == kReadyShared ? wino_auto_offset(kFires[f].e, kFires[f].sq) : 0);
+    return p;
+}
 }  // namespace
 
 // packed: the expand3x3 kernels of the eight fire layers as sq_pack_weights(SQ_F32) wrote them, or nullptr = they
@@ -770,32 +785,54 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     float *bufS = (float *)((char *)bufB + align_up(n * kBufB * 4, 256));
     float *means = (float *)((char *)bufS + align_up(n * kBufS * 4, 256));
     auto P = [&](int i) { return (const float *)params[i]; };
-    // transformed kernels of those expand3x3 layers whose algorithm wants them, written by
-    // one launch up front
+    // Kernels of the expand3x3 layers: packed ahead of time, or transformed by one launch up front where their algorithm
+    // wants that.  A tuning hook that asks for a form of the expands gets it from the workspace: packed kernels hold those
+    // that the rules here choose.
+    const bool forced = expand_form_forced();
+    const char *const ready_kernels = packed && !forced ? (const char *)packed : nullptr;
+    const int mask = g_fuse_pools_f32 >= 0 ? g_fuse_pools_f32 : fuse_pools_f32_policy(N);
+    // From ten images on the packed call runs layers on split operands, and its result is that of the unpacked call up to
+    // rounding; below, and in the unpacked call, the fp32 forms, which agree bit for bit whatever is pooled where.  The line is
+    // drawn so that a program that checks one call against the other with a few images finds no difference, not by time: the
+    // layers named first would gain from three images on.  us before / now: fire6 26.6 / 20.1 at 10 images, 56.5 / 46.2 at
+    // 64; fire8 33.9 / 24.1, 90.1 / 60.7; fire9 20.0 / 17.8, 33.3 / 26.3.
+    // With 16 and 32 squeeze layers from 32 images on: fire3 12.7 / 16.6 at 10 images, 20.4 / 19.7 at 24, 25.8 / 20.3 at
+    // 32, 39.8 / 35.1 at 64; fire5 18.6 / 23.9 at 16, 22.8 / 21.0 at 32, 36.1 / 25.0 at 64; but fire4 not where it
+    // pools the columns for the squeeze behind (with that squeeze, at 64 images 124 / 126, at 128 248 / 294).
+    const bool packed_forms = ready_kernels && !taps && N >= 10 && g_fuse_pools_f32 < 0;
+    char *const scratch_kernels = (char *)means + align_up(n * 1000 * 4, 256);
     char *conv_ws[8];
     size_t conv_ws_bytes[8];
-    bool conv_ws_ready[8];
+    int conv_ws_ready[8];
+    const void *split_e3[8] = {};
     KernelPrepJob prep[8];
     int nprep = 0;
     {
-        char *next = packed ? (char *)const_cast<void *>(packed) : (char *)means + align_up(n * 1000 * 4, 256);
+        char *next = scratch_kernels;
         int h = 55;
         for (int f = 0; f < 8; ++f) {
             const FireCfg &fc = kFires[f];
-            conv_ws[f] = next;
             conv_ws_bytes[f] = conv_workspace_bytes(fc.sq, fc.e, 3, 1, 1);
-            next += conv_ws_bytes[f];
-            ConvArgs a3 = make_args(bufS, params[2 + 6 * f + 4], nullptr, bufA, N, fc.sq, h, h, fc.e, 3, 1, 1, 1,
-                                    2 * fc.e, fc.e, SQ_F32);
-            a3.ws = conv_ws[f]; a3.ws_bytes = conv_ws_bytes[f];
-            conv_ws_ready[f] = packed != nullptr || conv_wants_prepared_kernels(a3, true);
-            if (conv_ws_ready[f] && !packed) prep[nprep++] = KernelPrepJob{params[2 + 6 * f + 4], conv_ws[f], fc.sq, fc.e};
+            if (ready_kernels) {
+                const PackedLayer at = packed_layer(f);
+                conv_ws[f] = const_cast<char *>(ready_kernels) + at.transforms;
+                conv_ws_ready[f] = at.ready;
+                if (packed_forms && (expand_split_shape(fc.sq, fc.e) || (N >= 32 && !(f == 2 && (mask & 16))))) split_e3[f] = ready_kernels + at.split;
+            } else {
+                conv_ws[f] = next;
+                next += conv_ws_bytes[f];
+                ConvArgs a3 = make_args(bufS, params[2 + 6 * f + 4], nullptr, bufA, N, fc.sq, h, h, fc.e, 3, 1, 1, 1,
+                                        2 * fc.e, fc.e, SQ_F32);
+                a3.ws = conv_ws[f]; a3.ws_bytes = conv_ws_bytes[f];
+                conv_ws_ready[f] = conv_wants_prepared_kernels(a3, true) ? kReadyBoth : 0;
+                if (conv_ws_ready[f]) prep[nprep++] = KernelPrepJob{params[2 + 6 * f + 4], conv_ws[f], fc.sq, fc.e};
+            }
             if (f == 2) h = 27;
             if (f == 6) h = 13;
         }
     }
     int rc = SQ_OK;
-    if (nprep && !packed) {
+    if (nprep) {
         set_stage("kernel transform");
         if ((rc = conv_prepare_kernels(prep, nprep, SQ_F32))) return rc;
     }
@@ -803,7 +840,6 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     // per element of the full map), `split` = columns pooled by the layer before, rows by that squeeze (ColPool: half
     // the bytes written and read); a split that has no kernel for its shape falls back to `inside`.  A call with
     // taps keeps every map, but runs the squeezes with the tiling the fused forms would use: same bits either way.
-    const int mask = g_fuse_pools_f32 >= 0 ? g_fuse_pools_f32 : fuse_pools_f32_policy(N);
     const int pools_in_squeeze = (mask | (mask >> 3)) & 7;
     const int fuse_pools = taps ? 0 : pools_in_squeeze;
     const int split_pools = taps ? 0 : (mask >> 3) & 7;
@@ -815,40 +851,13 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         cp.row_stride = colpool_row_stride(Wo, shift);
         return cp;
     };
-    // conv1, pool1 and the squeeze of fire2 in one launch where nobody asks for the maps between them.  The packed call from
-    // ten images on: below that, and in the unpacked call, the layers are the ones the two calls have in common bit for bit.
+    // conv1, pool1 and the squeeze of fire2 in one launch where nobody asks for the maps between them
     set_stage("conv1+pool1+fire2/sq");
     bool have_sq = false;
-    if (packed && !taps && N >= 10 && g_fuse_pools_f32 < 0) {
+    if (packed_forms) {
         rc = stem_split((const float *)in, P(0), P(1), P(2), P(3), bufS, N, 224, 224, 2, kFires[0].sq);
         if (rc != SQ_OK && rc != SQ_ERR_UNSUPPORTED) return rc;
         have_sq = rc == SQ_OK;
-    }
-    // In the same calls, expands on split operands, their expand3x3 kernels split by one launch into the part of the workspace
-    // where the unpacked call has its transformed ones.  With 48 and 64 squeeze layers at every such batch: us before / now at
-    // 10 images 26.6 / 20.1 (fire6), 33.9 / 24.1 (fire8), 20.0 / 17.8 (fire9); at 64 images 56.5 / 46.2, 90.1 / 60.7,
-    // 33.3 / 26.3.  With 16 and 32 from 32 images on: fire3 12.7 / 16.6 at 10 images, 20.4 / 19.7 at 24, 25.8 / 20.3 at
-    // 32, 39.8 / 35.1 at 64; fire5 18.6 / 23.9 at 16, 22.8 / 21.0 at 32, 36.1 / 25.0 at 64; but fire4 not where it
-    // pools the columns for the squeeze behind (with that squeeze, at 64 images 124 / 126, at 128 248 / 294).
-    const void *split_e3[8] = {}, *split_c10 = nullptr;
-    ConvArgs a10 = make_args(nullptr, params[50], P(51), nullptr, N, 512, 13, 13, 1000, 1, 1, 0, 1, 1000, 0, SQ_F32);
-    if (packed && !taps && N >= 10 && g_fuse_pools_f32 < 0 && !expand_form_forced()) {
-        SplitJob jobs[9];
-        int njobs = 0;
-        char *next = (char *)means + align_up(n * 1000 * 4, 256);
-        for (int f = 0; f < 8; ++f) {
-            const FireCfg &fc = kFires[f];
-            if (!expand_split_shape(fc.sq, fc.e) && (N < 32 || (f == 2 && (split_pools & 2)))) continue;
-            split_e3[f] = next;
-            jobs[njobs++] = SplitJob{params[2 + 6 * f + 4], next, fc.e, fc.sq, 3};
-            next += align_up(split_kernel_bytes(fc.e, fc.sq, 3), 256);
-        }
-        if (g_fuse_classifier < 0 && conv_avg_split_bytes(a10)) {
-            split_c10 = next;
-            jobs[njobs++] = SplitJob{params[50], next, 1000, 512, 1};
-        }
-        set_stage("kernel transform");
-        if ((rc = split_kernels(jobs, njobs))) return rc;
     }
     set_stage("conv1");
     ConvArgs a_conv1 = make_args(in, params[0], P(1), bufA, N, 3, 224, 224, 96, 7, 2, 2, 1, 96, 0, SQ_F32);
@@ -943,8 +952,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     // and probabilities.  A caller who wants to see the map gets it from an extra, plain run of the convolution; means
     // and probabilities come from the same two launches either way, so taps do not change them (the packed call from ten
     // images on excepted: its split operands are for calls without taps, and round differently).
-    a10.in = cur;
-    a10.out = nxt;
+    const ConvArgs a10 = make_args(cur, params[50], P(51), nxt, N, 512, H, H, 1000, 1, 1, 0, 1, 1000, 0, SQ_F32);
     set_stage("conv10");
     bool have_map = false;
     if (taps && taps[12]) {
@@ -953,7 +961,14 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         have_map = true;
     }
     AvgLayout lay;
-    rc = split_c10 ? conv_avg_split(a10, split_c10, bufS, n * kBufS * 4, &lay) : (int)SQ_ERR_UNSUPPORTED;
+    rc = SQ_ERR_UNSUPPORTED;
+    // On split operands, its kernels split here: both planes take 2.1 MB, which the packed kernels have no room for.  The launch
+    // costs 4 us of the 30 to 45 that it saves at 24 and 64 images; splitting inside the contraction instead cost 20.
+    const size_t c10_bytes = align_up(split_kernel_bytes(1000, 512, 1), 256);
+    if (packed_forms && g_fuse_classifier < 0 && conv_avg_split_bytes(a10) && scratch_kernels + c10_bytes <= base + workspace_bytes) {
+        if ((rc = split_kernels(P(50), scratch_kernels, 1000, 512, 1))) return rc;
+        rc = conv_avg_split(a10, scratch_kernels, bufS, n * kBufS * 4, &lay);
+    }
     if (rc == SQ_ERR_UNSUPPORTED && (g_fuse_classifier < 0 ? N >= 8 : g_fuse_classifier)) rc = conv_mfma_avg(a10, -1, bufS, n * kBufS * 4, &lay);
     if (rc == SQ_OK) {
         set_stage("avgpool+softmax");
@@ -995,13 +1010,16 @@ int sq_pack_weights(const void *const *params, int dtype, void *packed, size_t p
         if (!params[i]) return SQ_ERR_NULL;
     if (((uintptr_t)packed & 255) || packed_bytes < packed_f32_bytes()) return SQ_ERR_WORKSPACE;
     KernelPrepJob prep[8];
-    char *next = (char *)packed;
+    SplitJob split[8];
     for (int f = 0; f < 8; ++f) {
-        prep[f] = KernelPrepJob{params[2 + 6 * f + 4], next, kFires[f].sq, kFires[f].e};
-        next += conv_workspace_bytes(kFires[f].sq, kFires[f].e, 3, 1, 1);
+        const PackedLayer at = packed_layer(f);
+        const void *const w = params[2 + 6 * f + 4];
+        prep[f] = KernelPrepJob{w, (char *)packed + at.transforms, kFires[f].sq, kFires[f].e};
+        split[f] = SplitJob{w, (char *)packed + at.split, kFires[f].e, kFires[f].sq, 3};
     }
     set_stage("kernel transform");
-    const int rc = conv_prepare_kernels(prep, 8, SQ_F32);
+    int rc = conv_prepare_kernels(prep, 8, SQ_F32);
+    if (rc == SQ_OK) rc = split_kernels(split, 8);      // (second: over the layouts that are not needed)
     set_stage("");
     return rc;
 }

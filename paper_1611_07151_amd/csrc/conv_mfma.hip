@@ -36,7 +36,6 @@
 
 namespace sq {
 size_t wino_transformed_bytes(int Cout, int Cin);
-size_t wino_auto_offset(int Cout, int Cin);
 size_t wino_auto_bytes(int Cout, int Cin);
 namespace {
 
@@ -110,7 +109,8 @@ bool plan(const Variant &v, const ConvArgs &a, Plan &pl, const FusedE1 *e1 = nul
         return false;
     if (v.conv1_type && (a.Cin != 3 || a.Cout > 96 || a.Cout % 8 != 0)) return false;
     if (v.wino && (a.P != 1 || a.Cin % v.CC != 0 || a.Cout % 32 != 0 || !a.ws || ((uintptr_t)a.ws & 15) ||
-                   a.ws_bytes < conv_workspace_bytes(a.Cin, a.Cout, 3, 1, 1)))
+                   a.ws_bytes < conv_workspace_bytes(a.Cin, a.Cout, 3, 1, 1) ||
+                   (a.ws_ready && !(a.ws_ready & (v.wino_auto ? kReadyAuto : kReadyShared)))))
         return false;
 
     pl.blocks_y = 1;

@@ -129,7 +129,7 @@ int conv_s2d(const ConvArgs &a)
     a2.in = a.ws;
     a2.w = (const char *)a.ws + map_bytes;
     a2.Cin = s.C2; a2.H = s.H2; a2.W = s.W2; a2.K = s.K2; a2.S = 1; a2.P = 0;
-    a2.ws = nullptr; a2.ws_bytes = 0; a2.ws_ready = false;
+    a2.ws = nullptr; a2.ws_bytes = 0; a2.ws_ready = 0;
     // only where a matrix-core tiling serves the stride-1 form (its Ho, Wo are those of the call)
     if (conv_mfma_choice(a2) < 0) return SQ_ERR_UNSUPPORTED;
     int rc;

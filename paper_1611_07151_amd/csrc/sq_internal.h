@@ -51,6 +51,7 @@ struct ColPool {
 };
 inline int colpool_row_stride(int Wo, int shift) { const int Wp = (Wo - 3) / 2 + 1; return Wp + (Wp >> shift) + 2; }
 
+constexpr int kReadyShared = 1, kReadyAuto = 2, kReadyBoth = 3;
 struct ConvArgs {
     const void *in;
     const void *w;
@@ -61,7 +62,8 @@ struct ConvArgs {
     int dtype;  // sq_dtype of in and w
     void *ws;         // caller scratch some algorithms need (16-byte aligned), or nullptr
     size_t ws_bytes;
-    bool ws_ready;    // ws already holds this layer's transformed kernels (conv_prepare_kernels)
+    int ws_ready;     // layouts of this layer's transformed kernels (conv_prepare_kernels) that ws holds already: 0 = none,
+                      // kReadyShared, kReadyAuto (conv_wino_kernel.h's and conv_wino_auto_kernel.h's) or both
     // 1x1 convolution of a map that is max-pooled (3x3 window, stride 2, no padding) on the way in: extents of
     // the map in memory; H and W are then the pooled extents.  0 = the input is read as it is.
     int pool_H, pool_W;
@@ -145,6 +147,7 @@ struct KernelPrepJob {
     int Cin, Cout;
 };
 int conv_prepare_kernels(const KernelPrepJob *jobs, int n, int dtype);
+size_t wino_auto_offset(int Cout, int Cin);     // of the second layout in such an area
 // Whether this call will run an algorithm that works on transformed kernels; fire_expand says that it is the
 // expand3x3 of a fire layer, which may share a launch with the expand1x1 (conv_expand_pair).
 bool conv_wants_prepared_kernels(const ConvArgs &a, bool fire_expand);

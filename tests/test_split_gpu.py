@@ -378,3 +378,31 @@ def test_packed_fire_runs_the_kernels_of_the_unpacked_call_on_maps_of_any_width(
         names.append([r["name"] for r in sq.sq_profile_end() if "transform" not in r["name"] and "split_kernels" not in r["name"]])
     assert names[0] == names[1]
     assert torch.equal(*results)
+
+
+@pytest.mark.parametrize("n", [2, 3, 10, 33, 64])
+def test_packed_network_prepares_no_expand_kernels_inside_the_call(sq, n):
+    """Only conv10's kernels are prepared by the call itself, where it runs on split operands."""
+    cfg = synth.config_squeezenet(seed=60, n=min(n, 4))
+    params = [dev(p) for p in cfg["params"]]
+    x = dev(cfg["x"]).repeat((n + 3) // 4, 1, 1, 1)[:n].contiguous()
+    packed = sq.sq_pack_weights(params, sq.SQ_F32)
+    before = packed.clone()
+    sq.sq_profile_begin(128)
+    got = sq.sq_squeezenet_forward_packed(x, params, packed)
+    names = [r["name"] for r in sq.sq_profile_end()]
+    assert not any("transform" in k for k in names), names
+    assert [k for k in names if "split_kernels" in k] == (["conv10|split_kernels"] if n >= 16 else []), names
+    assert torch.equal(packed, before)
+    assert_close(got.cpu().numpy(), sq.sq_squeezenet_forward(x, params).cpu().numpy(), "packed and unpacked")
+    # forms that a tuning hook asks for are not among the packed kernels
+    for hook, forms in ((sq.lib.sq_tune_expand_pair, (1, 2, 3, 0)), (sq.lib.sq_tune_force_expand, (-3, -1))):
+        default = -1 if hook is sq.lib.sq_tune_expand_pair else -2
+        for form in forms:
+            try:
+                hook(form)
+                forced, want = sq.sq_squeezenet_forward_packed(x, params, packed), sq.sq_squeezenet_forward(x, params)
+            finally:
+                hook(default)
+            assert_close(forced.cpu().numpy(), want.cpu().numpy(), (hook, form))
+    assert torch.equal(packed, before)
