@@ -733,7 +733,8 @@ size_t sq_squeezenet_workspace_bytes(int N)
 // maps no longer stay in the memory-side cache between two layers and bytes count (whole pass 1010 -> 970 us at
 // batch 64, 1964 -> 1823 at 128, 3853 -> 3675 at 256; at batch 32 and below the split changes nothing or costs
 // 1-2 %: conv1 pays 8 % for the column maxima).  A call with taps keeps every pooled map, but runs the squeeze with
-// the tiling the fused forms would use, so the results are the same bit for bit.
+// the tiling the fused forms would use, so the results are the same bit for bit.  (In the packed call from ten images on
+// pool1 is part of the first launch, and fire8's split form writes a plain map: only pool4 is split there.)
 // The setter is a tuning hook, not part of the public interface.
 extern "C" void sq_tune_fuse_classifier(int on) { g_fuse_classifier = on < 0 ? -1 : on ? 1 : 0; }
 thread_local int g_fuse_pools_f32 = -1;
@@ -799,7 +800,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     // With 16 and 32 squeeze layers from 32 images on: fire3 12.7 / 16.6 at 10 images, 20.4 / 19.7 at 24, 25.8 / 20.3 at
     // 32, 39.8 / 35.1 at 64; fire5 18.6 / 23.9 at 16, 22.8 / 21.0 at 32, 36.1 / 25.0 at 64; but fire4 not where it
     // pools the columns for the squeeze behind (with that squeeze, at 64 images 124 / 126, at 128 248 / 294).
-    const bool packed_forms = ready_kernels && !taps && N >= 10 && g_fuse_pools_f32 < 0;
+    const bool packed_forms = ready_kernels && N >= 10 && g_fuse_pools_f32 < 0;
     char *const scratch_kernels = (char *)means + align_up(n * 1000 * 4, 256);
     char *conv_ws[8];
     size_t conv_ws_bytes[8];
@@ -851,7 +852,8 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         cp.row_stride = colpool_row_stride(Wo, shift);
         return cp;
     };
-    // conv1, pool1 and the squeeze of fire2 in one launch where nobody asks for the maps between them
+    // conv1, pool1 and the squeeze of fire2 in one launch; a caller who wants to see the maps between them gets them from extra,
+    // plain runs of the two layers
     set_stage("conv1+pool1+fire2/sq");
     bool have_sq = false;
     if (packed_forms) {
@@ -859,6 +861,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
         if (rc != SQ_OK && rc != SQ_ERR_UNSUPPORTED) return rc;
         have_sq = rc == SQ_OK;
     }
+    const bool see_conv1 = taps && (taps[0] || taps[1]);
     set_stage("conv1");
     ConvArgs a_conv1 = make_args(in, params[0], P(1), bufA, N, 3, 224, 224, 96, 7, 2, 2, 1, 96, 0, SQ_F32);
     if (!have_sq && (split_pools & 1)) {
@@ -872,7 +875,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
             cp_is_pending = true;
         }
     }
-    if (!have_sq && (rc = conv_mfma(a_conv1, -1))) return rc;
+    if ((!have_sq || see_conv1) && (rc = conv_mfma(a_conv1, -1))) return rc;
     if ((rc = copy_tap(taps, 0, bufA, n * 96 * 111 * 111))) return rc;
     // tiling of the squeeze behind pool `bit` when the pooled map is kept although the policy would not keep it
     auto squeeze_algo = [&](int bit, int f, int C, int H_in) {
@@ -886,6 +889,11 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     float *cur = bufA, *nxt = bufB;
     int pooled_from = 0;   // extent of the map `cur` before the pooling that the next squeeze is to do, or 0
     int sq_algo = squeeze_algo(1, 0, 96, 111);
+    if (have_sq && see_conv1) {
+        set_stage("pool1");
+        if ((rc = maxpool(bufA, bufB, N, 96, 111, 111, 3, 2))) return rc;
+        if ((rc = copy_tap(taps, 1, bufB, n * 96 * 55 * 55))) return rc;
+    }
     if (have_sq || (fuse_pools & 1)) {
         pooled_from = 111;
     } else {
@@ -950,8 +958,7 @@ static int squeezenet_f32(const void *in, const void *const *params, const void 
     // conv10 -> global average pooling -> softmax.  The convolution writes per-image plane sums of its results instead
     // of the 1000 x 13 x 13 map (which is then never written or read), and one more launch turns them into class means
     // and probabilities.  A caller who wants to see the map gets it from an extra, plain run of the convolution; means
-    // and probabilities come from the same two launches either way, so taps do not change them (the packed call from ten
-    // images on excepted: its split operands are for calls without taps, and round differently).
+    // and probabilities come from the same two launches either way, so taps do not change them.
     const ConvArgs a10 = make_args(cur, params[50], P(51), nxt, N, 512, H, H, 1000, 1, 1, 0, 1, 1000, 0, SQ_F32);
     set_stage("conv10");
     bool have_map = false;

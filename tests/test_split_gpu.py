@@ -406,3 +406,17 @@ def test_packed_network_prepares_no_expand_kernels_inside_the_call(sq, n):
                 hook(default)
             assert_close(forced.cpu().numpy(), want.cpu().numpy(), (hook, form))
     assert torch.equal(packed, before)
+
+
+@pytest.mark.parametrize("n", [10, 16, 33, 64])
+def test_taps_do_not_change_the_packed_network(sq, n):
+    cfg = synth.config_squeezenet(seed=61, n=min(n, 4))
+    params = [dev(p) for p in cfg["params"]]
+    x = dev(cfg["x"]).repeat((n + 3) // 4, 1, 1, 1)[:n].contiguous()
+    packed = sq.sq_pack_weights(params, sq.SQ_F32)
+    probs, taps = sq.sq_squeezenet_forward_packed(x, params, packed, want_taps=True)
+    assert torch.equal(sq.sq_squeezenet_forward_packed(x, params, packed), probs)
+    assert torch.equal(taps["probs"], probs)
+    want, wtaps = sq.sq_squeezenet_forward(x, params, want_taps=True)
+    for k in wtaps:         # (activations of order one: sums of much larger terms that cancel would differ by 2^-24 of those)
+        assert_close(taps[k].cpu().numpy(), wtaps[k].cpu().numpy(), k)
