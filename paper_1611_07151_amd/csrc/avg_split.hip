@@ -38,7 +38,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
     constexpr int plane = CK / 8 * kPix;
     __shared__ u32x4 patch[2 * plane];                        // [hi, lo][CK / 8][96][8 layers]
     __shared__ uint32_t top[kPix];                            // largest magnitude of a pixel so far
-    __shared__ int marks;                                     // 1: an infinity or NaN among them, 2: a pixel's layers are spread wide
+    __shared__ int odd_tile;                                  // an infinity or NaN among them
+    __shared__ int wide_pixel[kPix];                          // its layers are spread wide
 
     const int t = threadIdx.x, lane = t & 63, j = lane & 31, h = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -82,7 +83,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
         for (int k = 0; k < PER; ++k) {
             u32x4 hi, lo;
             const uint32_t m = top[q[k]];
-            if (m >= kOddMagnitude || spread(m, range[k].low)) atomicOr(&marks, m >= kOddMagnitude ? 1 : 2);
+            if (m >= kOddMagnitude) odd_tile = 1;
+            else if (spread(m, range[k].low)) wide_pixel[q[k]] = 1;
             split8(v[k], pow2(scale_exponent(m)), hi, lo);
             patch[t + k * NT] = hi;
             patch[t + k * NT + plane] = lo;
@@ -103,8 +105,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
     };
 #pragma unroll
     for (int k = 0; k < PER * 8; ++k) v[k >> 3][k & 7] = buf_ld(rin, off[k >> 3], (uint32_t)((k & 7) * p.HW) * 4u);
-    if (t < kPix) top[t] = 0;
-    if (t == 0) marks = 0;
+    if (t < kPix) { top[t] = 0; wide_pixel[t] = 0; }
+    if (t == 0) odd_tile = 0;
     __syncthreads();
     stage();
     // Steps of 16 layers: pixels are read one step ahead, kernels D steps, and a step asks for its share of the next layers
@@ -154,21 +156,25 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
         word[k] = p.sk[m];
         bias[k] = p.b ? p.b[m] : 0.f;
     }
-    int odd = marks & 1, wide = marks & 2;
+    int odd = odd_tile, wide = wide_pixel[j] | wide_pixel[32 + j] | wide_pixel[64 + j];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
         odd |= word[k] & kOddRow;
         wide |= word[k] & kWideRow;
     }
     // on the fp32 instructions from memory: an infinity or NaN, or sums too small for operands that are spread wide
-    bool again = __ballot(odd) != 0;
+    int again = __ballot(odd) ? 7 : 0;
     if (!again && __ballot(wide)) {
-        float least = kSmall;
 #pragma unroll
-        for (int pb = 0; pb < 3; ++pb)
+        for (int pb = 0; pb < 3; ++pb) {
+            float least = kSmall;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) least = fminf(least, ml + 8 * (k >> 2) + (k & 3) < p.Cout ? fabsf(main[pb][k]) : kSmall);
-        again = __ballot(least < kSmall) != 0;
+            for (int k = 0; k < 16; ++k) {
+                const bool marked = wide_pixel[pb * 32 + j] || (word[k] & kWideRow);
+                least = fminf(least, marked && ml + 8 * (k >> 2) + (k & 3) < p.Cout ? fabsf(main[pb][k]) : kSmall);
+            }
+            if (__ballot(least < kSmall)) again |= 1 << pb;
+        }
     }
 #pragma unroll
     for (int pb = 0; pb < 3; ++pb)
@@ -178,6 +184,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
         const rsrc_t rw = make_rsrc(p.raw, (uint32_t)(p.Cout * p.Cin) * 4u);
 #pragma unroll
         for (int pb = 0; pb < 3; ++pb) {
+            if (!(again >> pb & 1)) continue;
             const int gp = p0 + pb * 32 + j, n = fdiv(gp, p.dHW);
 #pragma unroll
             for (int k = 0; k < 16; ++k) main[pb][k] = 0.f;
@@ -189,7 +196,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void avg_split_kernel(const AvgParam
     for (int pb = 0; pb < 3; ++pb)
 #pragma unroll
         for (int k = 0; k < 16; ++k)
-            main[pb][k] = fmaxf(__builtin_amdgcn_ldexpf(main[pb][k], again ? 0 : -es[pb] - row_exponent(word[k])) + bias[k], 0.f);
+            main[pb][k] = fmaxf(__builtin_amdgcn_ldexpf(main[pb][k], again >> pb & 1 ? 0 : -es[pb] - row_exponent(word[k])) + bias[k], 0.f);
 
     // ---- plane sums per image: over a lane's three pixels, then over 32 lanes
     const int first = fdiv(p0, p.dHW), last = fdiv(min(p0 + kPix, p.PT) - 1, p.dHW);

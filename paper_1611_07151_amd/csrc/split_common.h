@@ -12,9 +12,12 @@
 // per pixel tile or pixel, chosen from the largest magnitude there, which comes to lie in [2^13, 2^14).  lo ends at 2^-24,
 // that is 2^-35 of hi's units: values from 2^-25 of the largest on keep all their bits, smaller ones are held to an
 // absolute 2^-36 (2^-49 of the largest).  That is no loss to a sum that a larger term reaches, but it is where the larger
-// ones meet zeros.  So tiles and output layers with a non-zero value below 2^-25 of their largest are marked (kWide), and of
-// their sums those that stay below kSmall (2^-20 of one large product and less: what the operands lose is then no longer
-// far below the sum) are made again on the fp32 instructions, from memory, as are all that an infinity or NaN may reach.
+// ones meet zeros.  So tiles and output layers with a non-zero value below 2^-27 of their largest are marked (kWide; a value
+// just above it still has 22 bits), and of their sums those that stay below kSmall (2^-22 of one large product and less: what
+// the operands lose is then no longer far below what the sum's own roundings are) are made again on the fp32
+// instructions, from memory, as are all that an infinity or NaN may reach.  Normally distributed values give a mark to
+// one tile or layer in some thousands, and such a sum to one call in some thousands (with marks from 2^-25 and sums below
+// 64 of all layers of a block: one call in twenty, 50 us each).
 #pragma once
 
 #include "conv_mfma_common.h"
@@ -30,8 +33,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_a4 __attribute__((aligned(4)));   // four floats at any fp32 address
 
 constexpr int kLowBits = 11;                       // lo is kept times 2^11
-constexpr uint32_t kWide = 25u << 23;              // spread of magnitudes (as bits) up to which every value keeps its bits
-constexpr float kSmall = 64.f;                     // sums of marked tiles and layers below this, scales included, are made again
+constexpr uint32_t kWide = 27u << 23;              // spread of magnitudes (as bits) from which a set is marked
+constexpr float kSmall = 16.f;                     // sums of marked tiles and layers below this, scales included, are made again
 // Range of the magnitudes of a set of values: the largest (NaN if one is), and the smallest but zero as twice its bits less
 // one (~0 if there is none).  Two instructions per value.
 struct Range {
@@ -115,20 +118,20 @@ __device__ __forceinline__ float joined(float main, float cross) { return __buil
 // Adds, on the fp32 matrix instructions, the products of one kernel tap: 32 output layers (lane j of either half: a layer)
 // x 32 pixels (lane j: a pixel) over Cin input layers, two at a time (half h: the second).  w_at and x_at are the lane's byte
 // offsets of layer h, or kOob for layers and pixels that are not there; the steps are the bytes between input layers.
-// Straight from memory, about ten times the time of the split form.
+// Straight from memory, some ten times the time of the split form.
 __device__ __forceinline__ f32x16 plain_tap(f32x16 acc, rsrc_t rw, uint32_t w_at, uint32_t w_step, rsrc_t rx, uint32_t x_at, uint32_t x_step, int Cin, int h)
 {
-    for (int c0 = 0; c0 < Cin; c0 += 8) {
-        float w[4], x[4];
+    for (int c0 = 0; c0 < Cin; c0 += 16) {
+        float w[8], x[8];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 8; ++k) {
             const uint32_t c = (uint32_t)(c0 + 2 * k);
             const bool there = (int)c + h < Cin;
             w[k] = buf_ld(rw, there ? w_at : kOob, c * w_step);
             x[k] = buf_ld(rx, there ? x_at : kOob, c * x_step);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc = Mfma<32>::run(w[k], x[k], acc);
+        for (int k = 0; k < 8; ++k) acc = Mfma<32>::run(w[k], x[k], acc);
     }
     return acc;
 }

@@ -294,13 +294,14 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
     const rsrc_t rout = make_rsrc(p.out, (uint32_t)((size_t)p.N * p.ldc * p.HW * 4));
     const float lowest = p.relu ? 0.f : -__builtin_inff();
 
-    // ---- a block of 32 output layers on the fp32 instructions, from memory
-    auto plain = [&](const float *w, int taps, int mb, int Cout, int coff, const int2 *sb) {
+    // ---- a block of 32 output layers on the fp32 instructions, from memory, for those pixel blocks that `which` names
+    auto plain = [&](int which, const float *w, int taps, int mb, int Cout, int coff, const int2 *sb) {
         const int side = taps == 1 ? 1 : K, reach = side / 2, m = mb * 32 + j;
         const rsrc_t rw = make_rsrc(w, (uint32_t)(Cout * p.Cin * taps) * 4u), rx = make_rsrc(p.in, (uint32_t)((size_t)p.N * p.Cin * p.HW * 4));
         const uint32_t wo = (uint32_t)((m * p.Cin + h) * taps) * 4u;
 #pragma unroll 1
         for (int pb = 0; pb < PB; ++pb) {
+            if (!(which >> pb & 1)) continue;
             const int gp = p0 + (grp * PB + pb) * 32 + j, gq = min(gp, p.PT - 1), n = fdiv(gq, p.dHW), pix = gq - n * p.HW, y = fdiv(pix, p.dW), x = pix - y * p.W;
             f32x16 sum;
 #pragma unroll
@@ -324,20 +325,23 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
     // ---- remove the scales, bias, ReLU; register 4q + i = layer 8q + 4h + i: 32 neighbouring pixels per store
     auto finish = [&](f32x16 (&main)[PB], f32x16 (&cross)[PB], int mb, int Cout, int coff, const int2 *sb, const int *words, const float *w, int taps) {
         const int word = words ? words[j] : sb[j].x;
-        bool again = odd || __ballot(word & kOddRow);
+        int again = odd || __ballot(word & kOddRow) ? (1 << PB) - 1 : 0;
         if (!again && (wide || __ballot(word & kWideRow))) {
-            float least = kSmall;
 #pragma unroll
-            for (int k = 0; k < 16; ++k)
+            for (int pb = 0; pb < PB; ++pb) {
+                float least = kSmall;
 #pragma unroll
-                for (int pb = 0; pb < PB; ++pb)
-                    least = fminf(least, mb * 32 + 8 * (k >> 2) + 4 * h + (k & 3) < Cout ? fabsf(main[pb][k]) : kSmall);
-            again = __ballot(least < kSmall) != 0;
+                for (int k = 0; k < 16; ++k) {
+                    const int ml = 8 * (k >> 2) + 4 * h + (k & 3);
+                    const bool marked = wide || ((words ? words[ml] : sb[ml].x) & kWideRow);
+                    least = fminf(least, marked && mb * 32 + ml < Cout ? fabsf(main[pb][k]) : kSmall);
+                }
+                if (__ballot(least < kSmall)) again |= 1 << pb;
+            }
         }
-        if (again) {
-            plain(w, taps, mb, Cout, coff, sb);
-            return;
-        }
+        uint32_t at[PB];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) at[pb] = again >> pb & 1 ? kOob : obase[pb];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -349,9 +353,10 @@ __global__ __launch_bounds__(512, 2) void expand_split_kernel(const ExpandParams
 #pragma unroll
                 for (int pb = 0; pb < PB; ++pb) {
                     const float v = fmaxf(__builtin_amdgcn_ldexpf(joined(main[pb][4 * q + i], cross[pb][4 * q + i]), ex) + __builtin_bit_cast(float, f.y), lowest);
-                    buf_st(rout, mb * 32 + ml < Cout ? obase[pb] : kOob, so, v);
+                    buf_st(rout, mb * 32 + ml < Cout ? at[pb] : kOob, so, v);
                 }
             }
+        if (again) plain(again, w, taps, mb, Cout, coff, sb);
     };
     auto clear = [&](f32x16 (&main)[PB], f32x16 (&cross)[PB]) {
 #pragma unroll

@@ -370,28 +370,30 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
                 mag = max((uint32_t)tops[0], (uint32_t)tops[1]);
                 const uint32_t low = min((uint32_t)lows[0], (uint32_t)lows[1]);
                 // The scale follows the largest magnitude met.  A step that would bring the sums before it down by 2^64 or
-                // more, that holds a value below 2^-25 of that magnitude, an infinity or NaN, and every step where the
+                // more, that holds a value below 2^-27 of that magnitude, an infinity or NaN, and every step where the
                 // kernels hold such values, is added up in fp32.
                 const bool up = mag > sq_limit;
                 const int en = up ? scale_exponent(mag) : sq_e;
                 const uint32_t made_for = up ? mag : max(sq_limit, 1u << 23) - (1u << 23);
                 if (__ballot(mag >= kOddMagnitude || spread(made_for, low) || (sq_limit && sq_e - en >= 64)) || red[8].y) {
-                    // (rare: kept small, its sums in LDS, so that the ordinary steps keep their registers)
-                    float *const own = reinterpret_cast<float *>(parts + wv * 128 + lane);
-#pragma unroll 1
-                    for (int r = 0; r < 8; ++r) {
-                        const int m = 8 * (r >> 2) + 4 * h + (r & 3);
-                        float *const to = own + (r >> 2) * 256 + (r & 3);
-                        const float *const w = p.wsq32 + (m < p.Csq ? m : 0) * 96 + cb * 32 + 16 * g;
-                        float add = plain ? *to : 0.f;
-#pragma unroll 1
-                        for (int k = 0; k < 16; ++k) {
-                            const int2 f = sb[cb * 32 + 16 * g + k];
-                            const float u = fmaxf(__builtin_amdgcn_ldexpf(pooled[ppc * S::MAP + 16 * g + k], scaled ? -es - f.x : 0) + __builtin_bit_cast(float, f.y), 0.f);
-                            add = __builtin_fmaf(u, w[k], add);
+                    f32x16 add;
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) add[k] = 0.f;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+                        if (plain) {
+                            const f32x4 old = parts[(wv * 2 + k) * 64 + lane];
+                            add[4 * k] = old.x; add[4 * k + 1] = old.y; add[4 * k + 2] = old.z; add[4 * k + 3] = old.w;
                         }
-                        *to = add;
+                    const float *const w = p.wsq32 + (j < p.Csq ? j : 0) * 96 + cb * 32 + 16 * g + h, *const from = pooled + ppc * S::MAP + 16 * g + h;
+#pragma unroll 2
+                    for (int k = 0; k < 8; ++k) {
+                        const int2 f = sb[cb * 32 + 16 * g + 2 * k + h];
+                        const float u = fmaxf(__builtin_amdgcn_ldexpf(from[2 * k], scaled ? -es - f.x : 0) + __builtin_bit_cast(float, f.y), 0.f);
+                        add = Mfma<32>::run(w[2 * k], u, add);
                     }
+                    parts[(wv * 2) * 64 + lane] = f32x4{add[0], add[1], add[2], add[3]};
+                    parts[(wv * 2 + 1) * 64 + lane] = f32x4{add[4], add[5], add[6], add[7]};
                     plain = true;
                     return;
                 }
