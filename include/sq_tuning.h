@@ -59,6 +59,10 @@ void sq_tune_expand_pair(int v);
  * 16 images (default), -1 = always, i >= 0 = always with tiling i of sq_conv_variant_name. */
 void sq_tune_force_expand(int v);
 
+/* fp32 3x3 and 5x5 layers with scratch, and the expands of fire layers called on their own, on split operands: 1 = wherever
+ * the form fits, 0 = never, -1 = where it is estimated to be faster (default). */
+void sq_tune_conv_split(int mode);
+
 /* Reduced-precision network: poolings inside the following squeeze (bits as above); -1 = default. */
 void sq_tune_fuse_pools(int mask);
 

@@ -137,6 +137,7 @@ int run_conv(const ConvArgs &a, int algo)
     if (a.pool_H && (algo == SQ_ALGO_DIRECT || a.K != 1 || a.S != 1 || a.P != 0)) return SQ_ERR_UNSUPPORTED;
     if (algo == SQ_ALGO_DIRECT) return conv_direct(a);
     if (algo == SQ_ALGO_AUTO) {
+        int variant = -1;               // where it is chosen on the way
         if (a.dtype == SQ_BF16 && a.ws) {   // bfloat16 operands and scratch: the bf16 matrix instructions where they pay
             const int rb = conv_bf16_mfma(a);
             if (rb != SQ_ERR_UNSUPPORTED && rb != SQ_ERR_WORKSPACE) return rb;
@@ -146,12 +147,12 @@ int run_conv(const ConvArgs &a, int algo)
             if (rs != SQ_ERR_UNSUPPORTED) return rs;
         }
         if (a.dtype == SQ_F32 && a.ws && !a.ws_ready) {
-            const int rp = conv_split(a);
+            const int rp = conv_split(a, &variant);
             if (rp != SQ_ERR_UNSUPPORTED) return rp;
         }
         const int r7 = conv7_split(a);
         if (r7 != SQ_ERR_UNSUPPORTED) return r7;
-        const int rc = conv_mfma(a, -1);
+        const int rc = conv_mfma(a, variant);
         if (rc != SQ_ERR_UNSUPPORTED || a.pool_H) return rc;   // only the tiled kernels pool on the way in
         return conv_direct(a);
     }
@@ -610,7 +611,9 @@ int fire_checked(const void *in, const void *w_sq, const float *b_sq, const void
     const size_t need = packed_e3 ? map_bytes : sq_fire_workspace_bytes(N, H, W, Csq, Ce3);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need) return SQ_ERR_WORKSPACE;
     if (packed_e3 && ((uintptr_t)packed_e3 & 255)) return SQ_ERR_WORKSPACE;
-    const bool split = expand_split_shape(Csq, Ce3);
+    const bool split = expand_split_shape(Csq, Ce3) &&
+                       expand_split_pays(make_args(in, w_e3, b_e3, out, N, Csq, H, W, Ce3, 3, 1, 1, 1, Ce1 + Ce3, Ce1, SQ_F32),
+                                         make_args(in, w_e1, b_e1, out, N, Csq, H, W, Ce1, 1, 1, 0, 1, Ce1 + Ce3, 0, SQ_F32));
     if (packed_e3) {
         const size_t transforms = conv_workspace_bytes(Csq, Ce3, 3, 1, 1);
         return fire_impl(in, w_sq, b_sq, w_e1, b_e1, w_e3, b_e3, out, N, Cin, H, W, Csq, Ce1, Ce3, (float *)workspace, const_cast<void *>(packed_e3),

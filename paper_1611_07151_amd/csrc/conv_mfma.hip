@@ -510,6 +510,35 @@ static int plan_expand_pair(const ConvArgs &a3, const ConvArgs &a1, Plan &p3, Pl
     return pair;
 }
 
+// Time in us of a 3x3 or 5x5 layer in the tiling of the automatic choice, linear in its estimate: fitted to 5000 shapes of their
+// own (8 to 512 input layers, maps of 7 to 56 pixels, 1 to 64 images), off by 3 to 10 % (root mean square) per kind of
+// tiling.  Infinite where there is no tiling.
+double conv_mfma_us(const ConvArgs &a, int *variant)
+{
+    Plan pl;
+    const int vi = choose_variant(a, pl);
+    *variant = vi;
+    if (vi < 0) return INFINITY;
+    const Variant &v = kVariants[vi];
+    const double e = estimate(v, pl, a) * 1e-6, kernels = (double)a.Cin * a.Cout * 1e-5;
+    if (v.wino_auto) return std::max(13.5, 13.3 + 1.67 * e + 25.0 * kernels);     // (with the transform of the kernels before it)
+    if (v.wino) return std::max(13.5, 12.7 + 2.05 * e + 8.0 * kernels);
+    if (v.KS == 5) return std::max(11.3, 6.3 + 2.94 * e);
+    if (v.BM == 64 && v.BN == 64) return std::max(11.3, 5.7 + 2.6 * e);
+    if (v.BM == 32 && v.BN == 32 && v.CC == 4) return std::max(11.3, 3.3 + 6.93 * e);
+    return std::max(11.3, 4.5 + 3.87 * e);
+}
+
+// The same for the expands of a fire layer of 48 or 64 squeeze layers as a pair, kernels transformed ahead (the autonomous form
+// on larger maps where the expand1x1 fits into it): 1500 shapes, off by 8 %.
+double expand_pair_us(const ConvArgs &a3, const ConvArgs &a1)
+{
+    const double tiles = (double)a3.N * ((a3.H + 1) / 2) * ((a3.W + 1) / 2), kernels = (double)a3.Cin * a3.Cout, products = 20e-9 * tiles * kernels;
+    if (a3.H * a3.W >= 27 * 27 && a1.Cout == a3.Cout) return 17.5 + 17.1 * products + 16.2e-5 * kernels;
+    const double rounds = ceil(ceil(tiles / kWinoBT) * ceil(a3.Cout / (double)kWinoBM) / (2.0 * num_cus()));
+    return 7.0 + 13.0 * products + 9.9 * rounds * a3.Cin / 64.0;
+}
+
 bool conv_expand_pair_supported(const ConvArgs &a3, const ConvArgs &a1)
 {
     Plan p3, p1;

@@ -2,8 +2,9 @@
 // (split_common.h): K x K layers on their own, and the expands of a fire layer (K x K and 1x1 of one map) in one launch.
 #include "split_common.h"
 
+#include <math.h>
+
 #include <algorithm>
-#include <type_traits>
 
 namespace sq {
 namespace split {
@@ -601,6 +602,23 @@ bool plan_expand(const ConvArgs &a, const ConvArgs *a1, const void *wk, ExpandPl
     return pl.lds <= (size_t)kLdsBytes;
 }
 
+// Time of a planned launch in us, with that of its kernels' split for a layer on its own: turns of a CU with one workgroup
+// and with two, each with its contraction steps, the staging of its patch (read twice where it is staged in parts) and its
+// stores.  Fitted to 3000 layers and 1500 fire layers' expands (16 to 512 input layers, maps of 7 to 56 pixels, 1 to 96
+// images): off by 6.5 % (root mean square).
+double expand_us(const ExpandPlan &pl)
+{
+    const ExpandParams &p = pl.p;
+    const bool pair = p.w1 != nullptr;
+    const double taps = p.K * p.K + (pair ? 1 : 0), nb = (p.Cout + 31) / 32, simd_waves = pl.waves / 4.0, units = ceil(nb / (p.cwn * pl.gy));
+    const bool two = 2 * pl.lds <= (size_t)kLdsBytes && pl.waves == 4;
+    const double turns = ceil((double)p.tiles * pl.gy / num_cus()), full = two ? floor(turns / 2) : 0.0, single = turns - 2 * full;
+    const double steps = units * p.G * taps / p.kg * pl.PB * simd_waves, staged = p.TP * p.G * 0.016 / simd_waves * (pl.parts ? 2 : 1);
+    const double us = (pair ? 9.0 : 10.0 + 2.46e-2 * nb * p.G * taps / 9) + single * (0.072 * steps + 0.307 * staged) + full * (0.136 * steps + 0.349 * staged) +
+                      (single + full) * 0.64 * units * pl.PB * simd_waves * (pair ? 2 : 1);
+    return pair ? us : std::max(13.2, us);
+}
+
 int launch_expand(const ExpandPlan &pl, const ConvArgs &a, const ConvArgs *a1)
 {
     ExpandFn fn = expand_fn(a.K, pl.PB, pl.parts);
@@ -618,13 +636,25 @@ int launch_expand(const ExpandPlan &pl, const ConvArgs &a, const ConvArgs *a1)
     return check_launch();
 }
 
+thread_local int g_conv_split = -1;
 }  // namespace
 
-int conv_split(const ConvArgs &a)
+extern "C" void sq_tune_conv_split(int mode) { g_conv_split = mode < 0 ? -1 : mode ? 1 : 0; }
+
+// Which layers on their own run in this form.  5x5 from 16 input layers on: all (1500 shapes, 0.96 to 14.8 times as fast as the
+// fp32 tilings).  3x3 from 16 on, where the estimate is 15 % below that of the other kernels, and 5x5 below 16 (a group
+// is 16, the rest padding), where it is below.  The launch that splits the kernels makes 3x3 layers lose below some 15 us;
+// those with few output layers over many input layers do at any size (with every such layer here: 384 -> 64 at 56x56, 16
+// images 125 us in the minimal-filtering form, 551 in this one; 64 -> 64 at 56x56 30 / 46).  Of 3060 3x3 shapes by
+// this rule 0.5 % lose over 3 %, and the mean gain is 1.28 of the 1.30 that the better of the two would give each time.
+int conv_split(const ConvArgs &a, int *variant)
 {
     ExpandPlan pl;
+    if (!g_conv_split) return SQ_ERR_UNSUPPORTED;
     if (!a.ws || ((uintptr_t)a.ws & 255) || a.ws_bytes < split_kernel_bytes(a.Cout, a.Cin, a.K)) return SQ_ERR_UNSUPPORTED;
     if (!plan_expand(a, nullptr, a.ws, pl)) return SQ_ERR_UNSUPPORTED;
+    if (g_conv_split < 0 && (a.K == 3 ? a.Cin < 16 || expand_us(pl) > 0.85 * conv_mfma_us(a, variant) : a.Cin < 16 && expand_us(pl) > conv_mfma_us(a, variant)))
+        return SQ_ERR_UNSUPPORTED;
     const int rc = split_kernels((const float *)a.w, a.ws, a.Cout, a.Cin, a.K);
     return rc ? rc : launch_expand(pl, a, nullptr);
 }
@@ -636,6 +666,16 @@ int conv_split(const ConvArgs &a)
 // 14.4 / 16.0 at 6 images, 20.1 / 21.2 at 16; 32 -> 128 at 27x27 20.0 / 21.2 at 16): their contraction is too short for
 // the patch that has to be split first.
 bool expand_split_shape(int Csq, int Ce3) { return Csq % 16 == 0 && Csq >= 48 && Csq <= 64 && Ce3 % 32 == 0; }
+
+// Whether it does in a fire layer called on its own: by estimate.  Of 1500 such shapes 5 % lost over 3 %, up to 38 % (64 -> 96
+// at 40x40, 48 images 57 / 92 us: three blocks of layers for four wavefronts; 48 -> 192 at 28x28, 64 images 57 / 65), with
+// the rule (7 % below the pair's estimate) 1.2 %, the worst 12 %; the mean gain is 1.18 without and 1.17 with it.
+bool expand_split_pays(const ConvArgs &a3, const ConvArgs &a1)
+{
+    ExpandPlan pl;
+    if (!g_conv_split || !plan_expand(a3, &a1, nullptr, pl)) return false;
+    return g_conv_split > 0 || expand_us(pl) < 0.93 * expand_pair_us(a3, a1);
+}
 
 int expand_split(const ConvArgs &a3, const ConvArgs &a1, const void *packed_e3)
 {

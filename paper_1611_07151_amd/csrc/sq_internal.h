@@ -97,6 +97,10 @@ int conv_mfma(const ConvArgs &a, int variant);
 int conv_expand_pair(const ConvArgs &a3, const ConvArgs &a1);
 // whether conv_expand_pair has a kernel for (a3, a1) -- nothing is launched
 bool conv_expand_pair_supported(const ConvArgs &a3, const ConvArgs &a1);
+// Estimated times in us of a 3x3 or 5x5 layer in the tiling of the automatic choice (and which it is; infinite and -1 where there
+// is none), and of a fire layer's expands as such a pair.
+double conv_mfma_us(const ConvArgs &a, int *variant);
+double expand_pair_us(const ConvArgs &a3, const ConvArgs &a1);
 // 1x1 convolution (+bias, ReLU) followed directly by a global average pooling: the convolution kernel writes per-image
 // plane sums of its results (a table of conv_mfma_avg_bytes() bytes, laid out as AvgLayout says) instead of the results;
 // avg_softmax() adds them up, divides by the plane size and applies softmax.  variant < 0 = the tiling of the
@@ -110,7 +114,8 @@ int avg_softmax(const float *sums, const AvgLayout &lay, float *means, float *pr
 // fp32 3x3 and 5x5 layers of stride 1 with "same" padding on the f16 matrix instructions (split_f32.hip), their kernels
 // split in a.ws (split_kernel_bytes() bytes); SQ_ERR_UNSUPPORTED where the form does not apply or the scratch is missing.
 size_t split_kernel_bytes(int Cout, int Cin, int K);
-int conv_split(const ConvArgs &a);
+// Also where it would be slower than the tiling of the automatic choice, which *variant then names.
+int conv_split(const ConvArgs &a, int *variant);
 struct SplitJob { const void *w; void *dst; int Cout, Cin, K; };
 int split_kernels(const SplitJob *jobs, int njobs);     // up to nine layers in one launch
 int split_kernels(const float *w, void *dst, int Cout, int Cin, int K);
@@ -123,6 +128,7 @@ bool split_register_kernels();
 // expand3x3 kernels from split_kernels(), or nullptr = split into a3.ws.
 bool expand_split_shape(int Csq, int Ce3);
 int expand_split(const ConvArgs &a3, const ConvArgs &a1, const void *packed_e3);
+bool expand_split_pays(const ConvArgs &a3, const ConvArgs &a1);     // in a fire layer on its own
 // The conv1 type (7x7, stride 2, three input layers, at most 96 output layers) on 16-bit matrix instructions (stem.hip):
 // alone in fp32 (split operands), or with the max pooling and the squeeze behind it in one launch -- fp32 (out: fp32 NCHW
 // map of the squeeze) or bfloat16 (packed kernels; out: blocked map).

@@ -16,6 +16,14 @@ def sq():
     return sq
 
 
+@pytest.fixture(autouse=True)
+def wherever_the_form_fits(sq):
+    """Layers too small for it to pay run on split operands too."""
+    sq.lib.sq_tune_conv_split(1)
+    yield
+    sq.lib.sq_tune_conv_split(-1)
+
+
 def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
@@ -420,3 +428,41 @@ def test_taps_do_not_change_the_packed_network(sq, n):
     want, wtaps = sq.sq_squeezenet_forward(x, params, want_taps=True)
     for k in wtaps:         # (activations of order one: sums of much larger terms that cancel would differ by 2^-24 of those)
         assert_close(taps[k].cpu().numpy(), wtaps[k].cpu().numpy(), k)
+
+
+# where the split form is the faster one and where it is not: 3x3 layers of one round of short launches, few output layers over
+# many input layers, 5x5 layers of any size; fire layers whose blocks of layers leave wavefronts idle
+@pytest.mark.parametrize("n,cin,cout,k,h,w_,split", [(1, 16, 64, 3, 7, 7, False), (16, 64, 64, 3, 14, 14, False), (1, 64, 256, 3, 28, 28, False), (16, 64, 64, 3, 56, 56, False),
+                                                     (4, 384, 64, 3, 56, 56, False), (4, 8, 384, 3, 56, 56, False), (7, 256, 384, 3, 13, 13, True), (4, 128, 256, 3, 27, 27, True),
+                                                     (1, 8, 40, 5, 7, 7, True), (16, 96, 256, 5, 27, 27, True), (2, 384, 16, 5, 40, 41, True)])
+def test_layers_run_in_the_faster_form(sq, n, cin, cout, k, h, w_, split):
+    rng = np.random.default_rng(n + cin)
+    x = synth.normal01(rng, (n, cin, h, w_))
+    w, b = synth.conv_params(rng, cout, cin, k)
+    pad = k // 2
+    names, results = [], []
+    for mode in (-1, 0, 1):
+        sq.lib.sq_tune_conv_split(mode)
+        sq.sq_profile_begin(8)
+        results.append(sq.sq_conv2d_forward_ws(dev(x), dev(w), dev(b), 1, pad, True).cpu().numpy())
+        names.append([r["name"] for r in sq.sq_profile_end()])
+    assert [any("_split_" in s for s in v) for v in names] == [split, False, True], names
+    for r in results:
+        assert_close(r, results[1], names)
+
+
+@pytest.mark.parametrize("n,csq,ce,h,w_,split", [(16, 48, 192, 27, 27, True), (64, 64, 256, 27, 27, True), (3, 64, 256, 13, 13, True), (48, 64, 96, 40, 40, False), (20, 64, 96, 56, 56, False)])
+def test_fire_layers_run_in_the_faster_form(sq, n, csq, ce, h, w_, split):
+    sq.lib.sq_tune_conv_split(-1)
+    rng = np.random.default_rng(n)
+    x = torch.rand((n, 16, h, w_), device="cuda")
+    d = [x] + [dev(a) for a in [*synth.conv_params(rng, csq, 16, 1), *synth.conv_params(rng, ce, csq, 1), *synth.conv_params(rng, ce, csq, 3)]]
+    names, results = [], []
+    for call, more in ((sq.sq_fire_forward, ()), (sq.sq_fire_forward_packed, (sq.sq_fire_pack_weights(d[5]),))):
+        sq.sq_profile_begin(8)
+        results.append(call(*d, *more))
+        names.append([r["name"] for r in sq.sq_profile_end()])
+    assert [any("_split_" in s for s in v) for v in names] == [split, split], names
+    assert torch.equal(*results)
+    sq.lib.sq_tune_conv_split(0)
+    assert_close(results[0].cpu().numpy(), sq.sq_fire_forward(*d).cpu().numpy(), names)
