@@ -718,8 +718,10 @@ struct ConvPlan {
 // one L2.  Expands at 64 images, us without / with: 16 -> 64 at 55x55 17.7 / 16.7, 32 -> 128 at 55x55 32.8 / 29.8; but
 // 48 -> 192 at 27x27 18.1 / 20.7, 64 -> 256 at 27x27 25.4 / 25.7, and 1x1 layers 128 -> 16 at 55x55 12.8 / 14.4,
 // 512 -> 1000 at 13x13 21.8 / 24.6, and a 3x3 layer with fp32 results at 55x55 167 / 170: with nothing to share,
-// neighbours only crowd the same channels.
-bool walks_rows(int H, int W) { return (long long)H * W >= 2048; }
+// neighbours only crowd the same channels.  Whole fire layers at 32 and 64 images, without / with: 40x52 21.7 / 23.3 and
+// 20.5 / 22.0 (16 -> 64), 46x46 21.7 / 23.2, 31.7 / 29.6, 20.3 / 21.5, 48x48 24.6 / 24.6, 33.8 / 31.2, 21.7 / 22.3, 50x50
+// 25.9 / 24.8, 35.6 / 32.4, 22.3 / 22.1, 56x51 26.4 / 24.8, 41.0 / 37.4, 22.6 / 22.4: never slower from 2450 pixels on.
+bool walks_rows(int H, int W) { return (long long)H * W >= 2450; }
 
 // Fills the launch parameters of one convolution; CB/PB/D = 0 lets this function choose.
 int plan_conv(ConvPlan &pl, const void *in, const void *wp, const float *b, void *out, int N, int Cin, int H, int W, int Cout,

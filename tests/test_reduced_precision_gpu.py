@@ -414,3 +414,9 @@ def test_expands_dealt_out_by_xcd_are_the_single_layers(sq, n, h, w, csq, ce1, c
     sq.sq_blocked_conv2d_forward(s, p[1], dev(b_e1), csq, ce1, 1, 0, True, out=out, c_offset=0)
     sq.sq_blocked_conv2d_forward(s, p[2], dev(b_e3), csq, ce3, 3, 1, True, out=out, c_offset=ce1)
     assert torch.equal(got.view(torch.int16), out.view(torch.int16))
+
+
+@pytest.mark.parametrize("n,h,w,csq,ce1,ce3", [(1, 50, 49, 16, 24, 40), (7, 35, 70, 32, 128, 96), (3, 49, 49, 16, 8, 64), (40, 51, 50, 48, 64, 64)])
+def test_expands_dealt_out_by_xcd_on_both_sides_of_the_line(sq, n, h, w, csq, ce1, ce3):
+    """The same on both sides of 2450 pixels, from which neighbouring tiles share an XCD."""
+    test_expands_dealt_out_by_xcd_are_the_single_layers(sq, n, h, w, csq, ce1, ce3)
