@@ -71,7 +71,8 @@ __global__ __launch_bounds__(256) void split_kernels_kernel(const SplitList list
             v[k] = m < Cout && c < Cin ? (at < row_in_lds ? row_lds[at] : row[at]) : 0.f;
         }
         u32x4 hi, lo;
-        split8(v, s, hi, lo);
+        float off = 0.f;
+        split8_kernel(v, s, hi, lo, off);
         const size_t at = ((((size_t)(m >> 5) * G + (c8 >> 1)) * KK + tap) * 2) * 64 + 32 * (c8 & 1) + (m & 31);
         wp[at] = hi;
         wp[at + 64] = lo;

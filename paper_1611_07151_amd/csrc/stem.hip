@@ -2,7 +2,8 @@
 // max pooling (3x3, stride 2) and the squeeze layer behind it.
 //
 // SPLIT: fp32 operands as two f16 values each (split_common.h); else bfloat16 operands (the reduced-precision network).
-// One k-group of eight values = the seven taps of a kernel row plus a zero = eight consecutive input pixels, as in
+// One k-group of eight values = the seven taps of a kernel row plus a zero (SPLIT: plus what rounding the seven loses) = eight
+// consecutive input pixels (SPLIT: seven, the last one twice), as in
 // conv7_bf16.hip: 11 steps of v_mfma_f32_32x32x16 for the 21 kernel rows.
 //
 // A workgroup of eight wavefronts works on a tile of 256 pixels of the layer; a wavefront owns 32 of them, keeps their
@@ -88,7 +89,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
     if (SPLIT && t == 0) { red[8] = uint2{0, 0}; red[9] = uint2{0, ~0u}; }
     if (POOL && t < 32) sbq[t] = int2{0, p.bsq && t < p.Csq ? __builtin_bit_cast(int, p.bsq[t]) : 0};
     // ---- kernels into LDS: [3 blocks][11 steps][NP][64 lanes][8]; lane l of step s = layer 32 * block + l % 32, kernel row
-    // 2 s + l / 32 of the 21 (the 22nd is zero), eighth value zero
+    // 2 s + l / 32 of the 21 (the 22nd is zero)
     if constexpr (SPLIT) {
         constexpr int kRows = 96 * 22, kPer = (kRows + S::THREADS - 1) / S::THREADS;
         float v[kPer][8];
@@ -119,7 +120,11 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
             const int e = t + k * S::THREADS, m = e / 22, r = e - 22 * m;
             if (e >= kRows) continue;
             u32x4 hi, lo;
-            split8(v[k], pow2(scale_exponent((uint32_t)sb[m].x)), hi, lo);
+            float off = 0.f;
+            split8_kernel(v[k], pow2(scale_exponent((uint32_t)sb[m].x)), hi, lo, off);
+            // the eighth place takes what the seven kernels of the row lose together, and meets the seventh pixel once more
+            const _Float16 rest = (_Float16)(off * (-1.f / (1 << kLowBits)));
+            hi[3] = (hi[3] & 0xffffu) | (uint32_t)__builtin_bit_cast(uint16_t, rest) << 16;
             const int at = ((m >> 5) * kSteps + (r >> 1)) * 128 + 32 * (r & 1) + (m & 31);
             wl[at] = hi;
             wl[at + 64] = lo;
@@ -216,7 +221,7 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
 #pragma unroll
             for (int q = 0; q < NP; ++q) {
                 u32x4 v = {at[q * S::PLANE], at[q * S::PLANE + 1], at[q * S::PLANE + 2], at[q * S::PLANE + 3]};
-                v.w &= 0xffffu;                                           // the eighth pixel is outside the window
+                v.w = SPLIT ? __builtin_amdgcn_perm(v.w, v.w, 0x01000100u) : v.w & 0xffffu;      // the eighth pixel is outside the window
                 b[s][q] = v;
             }
         }
@@ -302,9 +307,12 @@ __global__ __launch_bounds__(512, SPLIT ? 2 : 4) void stem_kernel(const Params p
             const uint32_t low = min(range.low, (uint32_t)__shfl_xor((int)range.low, 32, 64));
             if (top >= kOddMagnitude || spread(top, low)) red[8].y = 1;
             const int e = scale_exponent(top);
-            eight(wv, v);
             u32x4 hi, lo;
-            split8(v, pow2(e), hi, lo);
+            float off = 0.f;
+            for (int g = 0; g <= wv; ++g) {                 // (the errors of the steps before it with it)
+                eight(g, v);
+                split8_kernel(v, pow2(e), hi, lo, off);
+            }
             wq[(wv * 2) * 64 + lane] = hi;
             wq[(wv * 2 + 1) * 64 + lane] = lo;
             if (h == 0 && wv == 0) sbq[j].x = e;

@@ -466,3 +466,20 @@ def test_fire_layers_run_in_the_faster_form(sq, n, csq, ce, h, w_, split):
     assert torch.equal(*results)
     sq.lib.sq_tune_conv_split(0)
     assert_close(results[0].cpu().numpy(), sq.sq_fire_forward(*d).cpu().numpy(), names)
+
+
+def test_what_first_layer_kernels_lose_does_not_add_up_over_the_image(sq):
+    """Two f16 values hold a kernel value up to its last bit, and that error is the same at every pixel: the plane means of the
+    layer must be off by clearly less than kernels rounded one by one make them (r0, from the kernels themselves)."""
+    rng = np.random.default_rng(21)
+    x = synth.uniform01(rng, (4, 3, 112, 112))
+    w, _ = synth.conv_params(rng, 96, 3, 7)
+    top = 2.0 ** (13 - np.floor(np.log2(np.abs(w).max(axis=(1, 2, 3), keepdims=True))))
+    v = w.astype(np.float64) * top
+    hi = v.astype(np.float16).astype(np.float64)
+    lo = ((v - hi) * 2048).astype(np.float16).astype(np.float64) / 2048
+    pd = lambda k: torch.nn.functional.conv2d(dev(x).double(), torch.from_numpy(np.ascontiguousarray(k)).cuda(), None, 2, 2).mean((0, 2, 3))
+    r0 = pd((hi + lo - v) / top).pow(2).mean().sqrt().item()
+    got = sq.sq_conv2d_forward(dev(x), dev(w), None, 2, 2, False).double().mean((0, 2, 3))
+    off = (got - pd(w.astype(np.float64))).pow(2).mean().sqrt().item()
+    assert 0 < off < 0.6 * r0, (off, r0)
