@@ -273,7 +273,8 @@ def main() -> int:
     for r in recs:
         stage, kernel = r["name"].split("|")
         for table, key in ((kernels, kernel), (stages, stage)):
-            e = table.setdefault(key, dict(launches=0, ms=0.0, flops=0.0, bytes=0.0, mfma_flops=0.0))
+            e = table.setdefault(key, dict(launches=0, ms=0.0, flops=0.0, bytes=0.0, mfma_flops=0.0, peak_s=0.0))
+            e["peak_s"] += r["flops"] / 1e12 / (F16_MFMA_PEAK_TFLOPS / 3 if "_split" in kernel else FP32_MFMA_PEAK_TFLOPS)
             for f in ("launches", "ms", "flops", "bytes", "mfma_flops"):
                 e[f] += r[f]
     dom_name, dom = max(kernels.items(), key=lambda kv: kv[1]["ms"])
@@ -317,19 +318,21 @@ def main() -> int:
                             executed_tflops=round(e["mfma_flops"] / K / us / 1e6, 1) if e["flops"] else None,
                             gbs=round(e["bytes"] / K / us / 1e3, 0))
     # One row per module of the network (a fire layer = its squeeze and both expands; the classifier = conv10, average
-    # pooling and softmax): algorithmic TFLOP/s against the fp32 matrix peak and algorithmic GB/s against the HBM peak.
+    # pooling and softmax): algorithmic TFLOP/s, the share of the peak of the matrix instructions its kernels use (fp32, or a
+    # third of f16 for split operands), and algorithmic GB/s against the HBM peak.
     modules = {}
     for name, e in stages.items():
         mod = name.split("/")[0] if name.startswith("fire") else "classifier" if name in ("conv10", "avgpool", "softmax", "avgpool+softmax") else name
-        m = modules.setdefault(mod, dict(us=0.0, flops=0.0, bytes=0.0))
+        m = modules.setdefault(mod, dict(us=0.0, flops=0.0, bytes=0.0, peak_s=0.0))
+        m["peak_s"] += e["peak_s"] / K
         m["us"] += e["ms"] / K * 1e3
         m["flops"] += e["flops"] / K
         m["bytes"] += e["bytes"] / K
     for m in modules.values():
         tf, gb = m["flops"] / m["us"] / 1e6, m["bytes"] / m["us"] / 1e3
-        m.update(us=round(m["us"], 1), tflops=round(tf, 1), pct_fp32_mfma_peak=round(100 * tf / FP32_MFMA_PEAK_TFLOPS, 1),
+        m.update(us=round(m["us"], 1), tflops=round(tf, 1), pct_mfma_peak=round(100 * m["peak_s"] / (m["us"] * 1e-6), 1),
                  gbs=round(gb), pct_hbm_peak=round(100 * gb / HBM_PEAK_GBS, 1))
-        del m["flops"], m["bytes"]
+        del m["flops"], m["bytes"], m["peak_s"]
     # Every launch that does convolution work counts; the squeeze layers behind a max pooling do that pooling
     # while they read their input (kernel names "pool3s2+...", or "poolrows+..." where the layer before has already
     # pooled the columns), so the pooling time is in this figure too.

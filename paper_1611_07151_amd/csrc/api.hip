@@ -150,6 +150,8 @@ int run_conv(const ConvArgs &a, int algo)
             const int rp = conv_split(a, &variant);
             if (rp != SQ_ERR_UNSUPPORTED) return rp;
         }
+        // (the 7x7 layer has no lower line: with the pooling behind it, us before / now over 96 to 256 pixels: 20.6 / 19.9 at one
+        // image of 96, 20.0 / 20.6 at eight, 20.1 / 19.8 at one of 224, 35.0 / 24.8 at three; the worst of 54 sizes 3 % slower)
         const int r7 = conv7_split(a);
         if (r7 != SQ_ERR_UNSUPPORTED) return r7;
         const int rc = conv_mfma(a, variant);

@@ -7,8 +7,8 @@
 // workgroup's wavefronts share the pixels, which are staged CK input layers at a time: the next CK are on their way in
 // registers while these are multiplied.  Each pixel has a scale of its own, from the largest magnitude met so far; where
 // a later part of its layers needs a smaller one, its sums are brought down to that.
-// 512 -> 1000 layers at 13 x 13, launch alone, fp32 instructions / this: 32 images 62 / 24 us (720 TFLOP/s issued), 64
-// images 102 / 47.  Tiles of 64 pixels with four wavefronts per SIMD are no faster (27 and 47 us): what is left
+// 512 -> 1000 layers at 13 x 13, launch alone, fp32 instructions / this: 32 images 62 / 26 us (660 TFLOP/s issued), 64
+// images 102 / 51.  Tiles of 64 pixels with four wavefronts per SIMD are no faster (27 and 47 us): what is left
 // above the MFMAs' own time (11 us at 32 images) is not latency.
 #include "split_common.h"
 

@@ -15,8 +15,8 @@
 // contract the pooled pixels with the squeeze kernels.  Neither the layer's map (303 MB at batch 64 in fp32) nor the
 // pooled one exists in memory.
 // Measured at 64 images of 224 x 224: fp32 layer with pooling and squeeze 264 us (fp32 matrix instructions, two launches) ->
-// 146 us; bfloat16 92 us -> 71 us.  Eight images of 227 x 227, fp32 layer alone 77 us -> 29 us.  What SPLIT with POOL
-// spends beside its MFMAs (a third of the 146 us) is the way of the sums through LDS, two barriers per block of
+// 144 us; bfloat16 92 us -> 67 us.  Eight images of 227 x 227, fp32 layer alone 77 us -> 31 us.  What SPLIT with POOL
+// spends beside its MFMAs (a third of the 144 us) is the way of the sums through LDS, two barriers per block of
 // layers, which the one workgroup that fits a CU's LDS does not hide.
 // Ten wavefronts (two of them for the squeeze) need registers below 168 and spill: 240 us; eight at up to 256 do not.
 #include "split_common.h"
